@@ -985,7 +985,6 @@ __global__ void zero_tickets_kernel(int* p, int n) {
 
 // ------------------------------------------------------------------------- host side
 
-static int device_cus();
 // Ticket-claimed tiles (see gemm_bf16_pair_kernel): 1 by default, PCMOE_DYN=0 keeps every tile on the workgroup its
 // index implies, PCMOE_DYN=2 claims some tiles by ticket at any size.
 static int dynamic_tiles() {
@@ -1197,20 +1196,6 @@ static GemmArgs args_for(const moe_desc& d, const int32_t* offsets) {
   a.rows_cap = d.T * d.top_k;
   a.offsets = offsets;
   return a;
-}
-
-// Compute units of the current device (queried once per device).
-static int device_cus() {
-  static std::atomic<int> cus[64];  // 0 = not queried yet
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  int c = cus[dev].load(std::memory_order_relaxed);
-  if (c <= 0) {
-    int n = 0;
-    c = (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
-    cus[dev].store(c, std::memory_order_relaxed);
-  }
-  return c;
 }
 
 // Ragged-M contraction: n_cols output columns of the tile grid (FWD_GU: gate columns, two per pair).

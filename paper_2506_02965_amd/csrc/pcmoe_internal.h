@@ -160,6 +160,20 @@ inline hipError_t lds_limit_once(const void* kern, int bytes, std::atomic<uint64
   return e;
 }
 
+// Compute units of the current device (queried once per device).
+inline int device_cus() {
+  static std::atomic<int> cus[64];  // 0 = not queried yet
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  int c = cus[dev].load(std::memory_order_relaxed);
+  if (c <= 0) {
+    int n = 0;
+    c = (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
+    cus[dev].store(c, std::memory_order_relaxed);
+  }
+  return c;
+}
+
 // Launchers (defined next to their kernels). All return hipSuccess or the launch error.
 hipError_t launch_route_fwd(const moe_desc& d, const void* x, const void* wr, const float* bias, int bias_groups,
                             float* logits, int32_t* idx, float* w, hipStream_t s);

@@ -1,8 +1,8 @@
 // Gating (Alg. 7: scores, softmax, TopKIndices, w = p[I]) and its adjoint on the data owner.
 //
-// Scores are accumulated in fp64 (MFMA f64) from the exact products of the stored inputs and rounded
+// Scores are accumulated in fp64 (MFMA or FMA) from the exact products of the stored inputs and rounded
 // once to fp32, so the top-k decision is reproducible from the inputs alone. Selection happens at
-// wavefront level: k rounds of a 64-lane butterfly argmax on (score, -expert index).
+// wavefront level: k rounds of a 64-lane maximum over order-preserving keys, ties to the lowest expert index.
 #include "pcmoe_internal.h"
 #include <math.h>
 
@@ -10,232 +10,282 @@ namespace pcmoe {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-constexpr int RT_TOK = 16;  // tokens per workgroup (one MFMA row block)
+// Wavefront maximum of unsigned keys on the vector ALU (DPP: row shifts, then row broadcasts), in every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define PCMOE_DPP_MAX(ctrl, rows) \
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false))
+  PCMOE_DPP_MAX(0x111, 0xf);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds the row's maximum
+  PCMOE_DPP_MAX(0x112, 0xf);
+  PCMOE_DPP_MAX(0x114, 0xf);
+  PCMOE_DPP_MAX(0x118, 0xf);
+  PCMOE_DPP_MAX(0x142, 0xa);  // row_bcast 15 into rows 1 and 3, row_bcast 31 into rows 2 and 3
+  PCMOE_DPP_MAX(0x143, 0xc);
+#undef PCMOE_DPP_MAX
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
 
-// Scores of 16 tokens against all E experts on v_mfma_f64_16x16x4f64. The W wavefronts split d into
-// W equal ranges; their fp64 partial sums are added in a fixed order, the bias is added in fp64 and the
-// result is rounded once to fp32. Each lane feeds one 16-byte chunk of its token row and of its
-// expert row (8 bf16 / 4 fp32 consecutive k) into 8 / 4 MFMAs: MFMA s takes element s of every
-// lane, so lane group q contributes k = 4*EPC*c + EPC*q + s (the same mapping on both operands).
-// NET = 16-expert tiles per wavefront (E <= 16 * NET). Each wavefront then selects for 16 / W tokens.
-template <typename T, int NET, int W>
-__global__ __launch_bounds__(64 * W) void route_fwd_kernel(const T* __restrict__ x, const T* __restrict__ wr,
-                                                        const float* __restrict__ bias, int bias_div, int Tn,
-                                                        int d, int E, int k, int renorm,
-                                                        float* __restrict__ logits, int32_t* __restrict__ idx,
-                                                        float* __restrict__ gw) {
-  constexpr int EP = EPC<T>::value;   // elements per 16-byte chunk
-  constexpr int EW = 16 * NET + 1;    // padded expert stride of the partial-sum table
-  extern __shared__ double part[];    // [W waves][16 tokens][EW]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Order-preserving key of a score: larger score, larger key; -0 and +0 share one; 0 (below every number's) for a
+// NaN, which is never selected.
+__device__ __forceinline__ uint32_t score_key(float f) {
+  const uint32_t u = __float_as_uint(f);
+  if (f != f) return 0u;
+  if (f == 0.f) return 0x80000000u;
+  return (u >> 31) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ float key_score(uint32_t k) {
+  return k == 0u ? -INFINITY : __uint_as_float((k >> 31) ? (k & 0x7fffffffu) : ~k);
+}
+
+// Scores of NTOK = TB * TT tokens against all E experts on the fp64 matrix cores, then top-k and gate weights.
+// The WE x WK wavefronts split the experts into WE runs of 16 * NET and d into WK ranges of column steps (4 chunks
+// each); the WK fp64 partial sums of a score are added in a fixed order, the bias is added in fp64 and the result is
+// rounded once to fp32. Each lane feeds one 16-byte chunk of its token row and of its expert row (8 bf16 / 4 fp32
+// consecutive k) into 8 / 4 MFMAs: MFMA s takes element s of every lane, so lane group q contributes
+// k = 4*EPC*c + EPC*q + s (the same mapping on both operands).
+//   TB = 16: v_mfma_f64_16x16x4f64, 16 tokens x 16 experts.
+//   TB = 4:  v_mfma_f64_4x4x4_4b_f64, its four blocks one group of 4 tokens against 4 x 4 experts.
+//   TB = 1:  one token on v_fma_f64; lane group q's partial sums are added across the groups at the end.
+// All three do about 16 multiply-adds per cycle and SIMD (a 16 x 16 x 4 product takes 64 cycles, measured), and the
+// vector ALU does not run beside an fp64 MFMA: the bound is the products and, at 8 cycles each, the conversions to
+// fp64 (T = 16384, E = 64, d = 2048: 4.3 GFLOP, 56 us of products, 86 us measured, 108 before). A workgroup's
+// products run on one CU, so a short batch takes workgroups of few tokens: 16 tokens x 64 experts x d = 2048 alone
+// are 14 us of a CU's fp64 rate, whatever the token count. Long batches take TT token tiles per wavefront: an expert
+// chunk is then converted once for TT products, a token chunk once for NET.
+// PF column steps of loads are in flight per wavefront.
+template <typename T, int TB, int TT, int NET, int WE, int WK, int PF>
+__global__ __launch_bounds__(64 * WE * WK) void route_fwd_kernel(const T* __restrict__ x, const T* __restrict__ wr,
+                                                              const float* __restrict__ bias, int bias_div, int Tn,
+                                                              int d, int E, int k, int renorm,
+                                                              float* __restrict__ logits, int32_t* __restrict__ idx,
+                                                              float* __restrict__ gw) {
+  constexpr int EP = EPC<T>::value;        // elements per 16-byte chunk
+  constexpr int EW = 16 * NET * WE + 1;    // padded expert stride of the partial-sum table
+  constexpr int NTOK = TB * TT;
+  constexpr int W = WE * WK;
+  extern __shared__ double part[];         // [WK][NTOK][EW]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int we = wave % WE, wk = wave / WE;
   const int i = lane & 15, q = lane >> 4;
-  const int t0 = blockIdx.x * RT_TOK;
-  const int t = t0 + i;
-  const int kq = d / W;
-  const int kb = wave * kq;
-  // CH independent accumulator chains per expert tile (column steps alternate between them), added in
-  // chain order at the end: back-to-back MFMAs on one accumulator wait for each other.
-  constexpr int CH = NET <= 4 ? 2 : 1;
-  doublex4 acc[CH][NET];
+  const int t0 = blockIdx.x * NTOK;
+  const int e0 = we * 16 * NET;
+  // Column steps [s0, s1) of this wavefront.
+  const int steps = d / (4 * EP);
+  const int s0 = (int)((long)steps * wk / WK), s1 = (int)((long)steps * (wk + 1) / WK);
+  const T* xrow[TT];
+  const T* wrow[NET];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) {
+    const int t = t0 + tt * TB + (TB == 16 ? i : TB == 4 ? (lane & 3) : 0);
+    xrow[tt] = x + (size_t)(t < Tn ? t : Tn - 1) * d + EP * q;  // rows past the end: a valid row, never used
+  }
+#pragma unroll
+  for (int et = 0; et < NET; ++et) {
+    const int e = e0 + 16 * et + i;
+    wrow[et] = wr + (size_t)(e < E ? e : E - 1) * d + EP * q;   // as above
+  }
+  typedef typename std::conditional<TB == 16, doublex4, double>::type Acc;
+  // CH independent accumulator chains per product (column steps alternate between them), added in chain order
+  // at the end: back-to-back MFMAs on one accumulator wait for each other.
+  constexpr int CH = TT * NET >= 8 ? 1 : TT * NET >= 4 ? 2 : 4;
+  Acc acc[CH][TT][NET];
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch)
 #pragma unroll
-    for (int et = 0; et < NET; ++et) acc[ch][et] = doublex4{0.0, 0.0, 0.0, 0.0};
-  const T* xrow = x + (size_t)(t < Tn ? t : 0) * d;
-  // Column steps of 4 chunks; the loads of the next two steps are in flight while one step computes.
-  const int nstep = kq / (4 * EP);
-  auto load = [&](int st, Chunk& xc, Chunk (&wc)[NET]) {
-    const int c = kb + st * 4 * EP + EP * q;
-    xc = t < Tn ? ld_chunk(xrow + c) : zero_chunk();
+    for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-    for (int et = 0; et < NET; ++et) {
-      const int e = 16 * et + i;
-      wc[et] = e < E ? ld_chunk(wr + (size_t)e * d + c) : zero_chunk();
+      for (int et = 0; et < NET; ++et) {
+        if constexpr (TB == 16) acc[ch][tt][et] = doublex4{0.0, 0.0, 0.0, 0.0};
+        else acc[ch][tt][et] = 0.0;
+      }
+  Chunk xc[PF][TT], wc[PF][NET];
+  auto load = [&](int st, Chunk (&xb)[TT], Chunk (&wb)[NET]) {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) xb[tt] = ld_chunk(xrow[tt] + st * 4 * EP);
+#pragma unroll
+    for (int et = 0; et < NET; ++et) wb[et] = ld_chunk(wrow[et] + st * 4 * EP);
+  };
+  auto compute = [&](const Chunk (&xb)[TT], const Chunk (&wb)[NET]) {
+    float xf[TT][EP], wf[NET][EP];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) chunk_to_f<T>(xb[tt], xf[tt]);
+#pragma unroll
+    for (int et = 0; et < NET; ++et) chunk_to_f<T>(wb[et], wf[et]);
+#pragma unroll
+    for (int s = 0; s < EP; ++s) {
+      double xd[TT], wd[NET];
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) xd[tt] = (double)xf[tt][s];
+#pragma unroll
+      for (int et = 0; et < NET; ++et) wd[et] = (double)wf[et][s];
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int et = 0; et < NET; ++et) {
+          Acc& a = acc[s % CH][tt][et];
+          if constexpr (TB == 16) a = __builtin_amdgcn_mfma_f64_16x16x4f64(xd[tt], wd[et], a, 0, 0, 0);
+          else if constexpr (TB == 4) a = __builtin_amdgcn_mfma_f64_4x4x4f64(wd[et], xd[tt], a, 0, 0, 0);
+          else a = fma(xd[tt], wd[et], a);
+        }
     }
   };
-  auto compute = [&](const Chunk& xc, const Chunk (&wc)[NET]) {
-    float xf[EP];
-    chunk_to_f<T>(xc, xf);
 #pragma unroll
-    for (int et = 0; et < NET; ++et) {
-      float wf[EP];
-      chunk_to_f<T>(wc[et], wf);
+  for (int u = 0; u < PF; ++u)
+    if (s0 + u < s1) load(s0 + u, xc[u], wc[u]);
+  for (int st = s0; st < s1; st += PF) {
 #pragma unroll
-      for (int s = 0; s < EP; ++s)
-        acc[s % CH][et] =
-            __builtin_amdgcn_mfma_f64_16x16x4f64((double)xf[s], (double)wf[s], acc[s % CH][et], 0, 0, 0);
-    }
-  };
-  Chunk xa, xb, wa[NET], wb[NET];
-  if (nstep > 0) load(0, xa, wa);
-  if (nstep > 1) load(1, xb, wb);
-  for (int st = 0; st < nstep; st += 2) {
-    compute(xa, wa);
-    if (st + 2 < nstep) load(st + 2, xa, wa);
-    if (st + 1 < nstep) {
-      compute(xb, wb);
-      if (st + 3 < nstep) load(st + 3, xb, wb);
+    for (int u = 0; u < PF; ++u) {
+      if (st + u < s1) {
+        compute(xc[u], wc[u]);
+        if (st + u + PF < s1) load(st + u + PF, xc[u], wc[u]);
+      }
     }
   }
-  // f64 16x16x4 output: register r of lane group q holds D[token 4r + q][expert 16 et + i]
+  // 16x16x4: register r of lane group q holds D[token 4r + q][expert i]. 4x4x4: lane l holds token l & 3 and expert
+  // 4 * ((l >> 2) & 3) + (l >> 4). One token: every lane group holds its own columns' sum for expert i.
 #pragma unroll
-  for (int et = 0; et < NET; ++et)
+  for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double a = acc[0][et][r];
+    for (int et = 0; et < NET; ++et) {
+      Acc a = acc[0][tt][et];
 #pragma unroll
-      for (int ch = 1; ch < CH; ++ch) a += acc[ch][et][r];
-      part[(wave * 16 + 4 * r + q) * EW + 16 * et + i] = a;
+      for (int ch = 1; ch < CH; ++ch) a += acc[ch][tt][et];
+      if constexpr (TB == 16) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          part[(wk * NTOK + tt * 16 + 4 * r + q) * EW + e0 + 16 * et + i] = a[r];
+      } else if constexpr (TB == 4) {
+        part[(wk * NTOK + tt * 4 + (lane & 3)) * EW + e0 + 16 * et + (lane & 12) + q] = a;
+      } else {
+        a += __shfl_xor(a, 16, 64);
+        a += __shfl_xor(a, 32, 64);
+        if (q == 0) part[(wk * NTOK + tt) * EW + e0 + 16 * et + i] = a;
+      }
     }
   __syncthreads();
 
-  // TW tokens per wavefront: fixed-order sum of the W partials, bias, one rounding, then top-k. The
-  // tokens of a wavefront go through the cross-lane argmax rounds together, so their shuffle latencies
-  // overlap.
-  constexpr int TW = RT_TOK / W;  // tokens per wavefront
-  float v[TW][4];
-  bool taken[TW][4];
-#pragma unroll
-  for (int rr = 0; rr < TW; ++rr) {
-    const int row = wave * TW + rr;
+  // Each wavefront finishes tokens wave, wave + W, ...: fixed-order sum of the WK partials, bias, one rounding, then
+  // k rounds of the wavefront maximum over order-preserving keys (lowest expert index among equal scores).
+  constexpr int QE = (16 * NET * WE + 63) / 64;  // experts per lane: lane, lane + 64, ...
+  for (int row = wave; row < NTOK; row += W) {
     const int tt = t0 + row;
+    if (tt >= Tn) break;
+    uint32_t key[QE];
+    float v[QE];
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq) {
+    for (int qq = 0; qq < QE; ++qq) {
       const int e = lane + 64 * qq;
-      v[rr][qq] = -INFINITY;
-      taken[rr][qq] = true;
-      if (tt < Tn && e < E) {
+      v[qq] = -INFINITY;
+      key[qq] = 0u;
+      if (e < E) {
         double sum = part[row * EW + e];
 #pragma unroll
-        for (int w = 1; w < W; ++w) sum += part[(w * 16 + row) * EW + e];
+        for (int w = 1; w < WK; ++w) sum += part[(w * NTOK + row) * EW + e];
         if (bias) sum += (double)bias[(size_t)(tt / bias_div) * E + e];
         const float L = (float)sum;
         logits[(size_t)tt * E + e] = L;
-        v[rr][qq] = L;
-        taken[rr][qq] = false;
+        v[qq] = L;
+        key[qq] = score_key(L);
       }
     }
-  }
-  float myv[TW], bv[TW];
-  int myi[TW], bi[TW];
+    float myv = -INFINITY;
+    int myi = 0;
+    for (int j = 0; j < k; ++j) {
+      uint32_t m = key[0];
 #pragma unroll
-  for (int rr = 0; rr < TW; ++rr) {
-    myv[rr] = -INFINITY;
-    myi[rr] = 0;
-  }
-  for (int j = 0; j < k; ++j) {
+      for (int qq = 1; qq < QE; ++qq) m = max(m, key[qq]);
+      m = wave_max_u32(m);
+      int best = 0x7fffffff;  // no selectable score is left (NaN scores only)
+      if (m != 0u) {
 #pragma unroll
-    for (int rr = 0; rr < TW; ++rr) {
-      bv[rr] = -INFINITY;
-      bi[rr] = 0x7fffffff;
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq) {
-        const int e = lane + 64 * qq;
-        if (!taken[rr][qq] && (v[rr][qq] > bv[rr] || (v[rr][qq] == bv[rr] && e < bi[rr]))) {
-          bv[rr] = v[rr][qq];
-          bi[rr] = e;
+        for (int qq = QE - 1; qq >= 0; --qq) {
+          const uint64_t b = __ballot(key[qq] == m);
+          if (b) best = 64 * qq + __builtin_ctzll(b);
         }
       }
-    }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      float ov[TW];
-      int oi[TW];
-#pragma unroll
-      for (int rr = 0; rr < TW; ++rr) {
-        ov[rr] = __shfl_xor(bv[rr], off, 64);
-        oi[rr] = __shfl_xor(bi[rr], off, 64);
-      }
-#pragma unroll
-      for (int rr = 0; rr < TW; ++rr)
-        if (ov[rr] > bv[rr] || (ov[rr] == bv[rr] && oi[rr] < bi[rr])) {
-          bv[rr] = ov[rr];
-          bi[rr] = oi[rr];
-        }
-    }
-#pragma unroll
-    for (int rr = 0; rr < TW; ++rr) {
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq)
-        if (lane + 64 * qq == bi[rr]) taken[rr][qq] = true;
+      for (int qq = 0; qq < QE; ++qq)
+        if (lane + 64 * qq == best) key[qq] = 0u;
       if (lane == j) {
-        myv[rr] = bv[rr];
-        myi[rr] = bi[rr];
+        myv = key_score(m);
+        myi = best;
       }
     }
-  }
-  float ex[TW], zp[TW];
+    const float m = __shfl(myv, 0, 64);  // the largest score of the token
+    const float ex = (lane < k) ? expf(myv - m) : 0.f;
+    float zp = ex;
+    if (!renorm) {
+      zp = 0.f;
 #pragma unroll
-  for (int rr = 0; rr < TW; ++rr) {
-    const float m = __shfl(myv[rr], 0, 64);  // the largest score of the token
-    ex[rr] = (lane < k) ? expf(myv[rr] - m) : 0.f;
-    if (renorm) {
-      zp[rr] = ex[rr];
-    } else {
-      zp[rr] = 0.f;
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq)
-        if (lane + 64 * qq < E) zp[rr] += expf(v[rr][qq] - m);
+      for (int qq = 0; qq < QE; ++qq)
+        if (lane + 64 * qq < E) zp += expf(v[qq] - m);
+    }
+    zp = wave_sum(zp);
+    if (lane < k) {
+      idx[(size_t)tt * k + lane] = myi;
+      gw[(size_t)tt * k + lane] = ex / zp;
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-    for (int rr = 0; rr < TW; ++rr) zp[rr] += __shfl_xor(zp[rr], off, 64);
-#pragma unroll
-  for (int rr = 0; rr < TW; ++rr) {
-    const int tt = t0 + wave * TW + rr;
-    if (tt < Tn && lane < k) {
-      idx[(size_t)tt * k + lane] = myi[rr];
-      gw[(size_t)tt * k + lane] = ex[rr] / zp[rr];
-    }
+}
+
+template <typename T, int TB, int TT, int NET, int WE, int WK, int PF>
+static hipError_t route_fwd_run(const moe_desc& d, const void* x, const void* wr, const float* bias, int div,
+                                float* logits, int32_t* idx, float* w, hipStream_t s) {
+  constexpr int NTOK = TB * TT;
+  constexpr size_t LDS = (size_t)WK * NTOK * (16 * NET * WE + 1) * sizeof(double);
+  static_assert(LDS <= 160 * 1024, "partial-sum table");
+  auto kern = route_fwd_kernel<T, TB, TT, NET, WE, WK, PF>;
+  if (LDS > 65536) {
+    static std::atomic<uint64_t> lds_set{0};
+    if (hipError_t e = lds_limit_once((const void*)kern, (int)LDS, lds_set); e != hipSuccess) return e;
   }
+  KernelTimer kt("route_fwd", s);
+  hipLaunchKernelGGL(kern, dim3((d.T + NTOK - 1) / NTOK), dim3(64 * WE * WK), LDS, s, (const T*)x, (const T*)wr, bias,
+                     div, d.T, d.d_model, d.n_experts, d.top_k, d.renormalize, logits, idx, w);
+  return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t route_fwd_t(const moe_desc& d, const void* x, const void* wr, const float* bias, int bg,
                               float* logits, int32_t* idx, float* w, hipStream_t s) {
   const int E = d.n_experts;
-  dim3 grid((d.T + RT_TOK - 1) / RT_TOK);
   const int div = d.T / (bg > 0 ? bg : 1);
-  KernelTimer kt("route_fwd", s);
-  // Wavefronts per workgroup: as many as split d into whole column steps (4 chunks) and keep the
-  // partial-sum table within 64 KB (all 4 beyond that: d is a multiple of 128).
-  constexpr int STEP = 4 * EPC<T>::value;
-  auto waves_for = [&](int net) {
-    for (int wv = 16; wv > 4; wv >>= 1)
-      if (d.d_model % (wv * STEP) == 0 && (size_t)wv * 16 * (16 * net + 1) * sizeof(double) <= 65536) return wv;
-    return 4;
-  };
-#define RT_LAUNCH_W(NET, W)                                                                                     \
-  do {                                                                                                          \
-    const size_t lds = (size_t)W * 16 * (16 * NET + 1) * sizeof(double);                                       \
-    if (lds > 65536) {                                                                                          \
-      static std::atomic<uint64_t> lds_set_{0};                                                                 \
-      hipError_t e_ = lds_limit_once((const void*)route_fwd_kernel<T, NET, W>, (int)lds, lds_set_);             \
-      if (e_ != hipSuccess) return e_;                                                                          \
-    }                                                                                                           \
-    hipLaunchKernelGGL((route_fwd_kernel<T, NET, W>), grid, dim3(64 * W), lds, s, (const T*)x, (const T*)wr,     \
-                       bias, div, d.T, d.d_model, E, d.top_k, d.renormalize, logits, idx, w);                   \
-  } while (0)
-  // (the table limit leaves 16 wavefronts to NET = 1 and 8 to NET <= 2)
+  // Tokens per workgroup: the fewest (1, 4, 16 or 32) whose workgroups are at most one per CU, since a workgroup costs
+  // its padded tokens' products and a second round costs as much as the first. Measured on MI355X (d = 2048, E = 64;
+  // us for 1 / 4 / 16 / 32 tokens): T = 24 12 / 14 / - / -, T = 300 22 / 15 / 26 / 43, T = 3000 - / 48 / 26 / 43,
+  // T = 8192 - / - / 50 / 44; the 16-token workgroups of 4 wavefronts used before took 36, 37, 37 and 57.
+  // Wavefronts: as many as fit the LDS table and, at 16 of them, 128 VGPRs without spills.
+#define RT(TB, TT, NET, WE, WK, PF) \
+  return route_fwd_run<T, TB, TT, NET, WE, WK, PF>(d, x, wr, bias, div, logits, idx, w, s)
+  const int cus = device_cus();
+  const int tok = d.T <= cus ? 1 : d.T <= 4 * cus ? 4 : d.T <= 16 * cus ? 16 : 32;
   if (E <= 16) {
-    const int wv = waves_for(1);
-    if (wv == 16) RT_LAUNCH_W(1, 16);
-    else if (wv == 8) RT_LAUNCH_W(1, 8);
-    else RT_LAUNCH_W(1, 4);
+    if (tok == 1) RT(1, 1, 1, 1, 16, 4);
+    if (tok == 4) RT(4, 1, 1, 1, 16, 4);
+    if (tok == 16) RT(16, 1, 1, 1, 16, 4);
+    RT(16, 1, 1, 1, 8, 4);  // one expert tile: 32 tokens per workgroup measured slower (28 against 30 us at d = 4096)
   } else if (E <= 32) {
-    if (waves_for(2) == 8) RT_LAUNCH_W(2, 8);
-    else RT_LAUNCH_W(2, 4);
+    if (tok == 1) RT(1, 1, 2, 1, 16, 4);
+    if (tok == 4) RT(4, 1, 2, 1, 16, 4);
+    if (tok == 16) RT(16, 1, 2, 1, 8, 3);
+    RT(16, 2, 2, 1, 8, 2);
   } else if (E <= 64) {
-    RT_LAUNCH_W(4, 4);
+    if (tok == 1) RT(1, 1, 4, 1, 16, 2);
+    if (tok == 4) RT(4, 1, 4, 1, 16, 2);
+    if (tok == 16) RT(16, 1, 4, 1, 8, 2);
+    RT(16, 2, 4, 1, 8, 2);
   } else if (E <= 128) {
-    RT_LAUNCH_W(8, 4);
+    if (tok == 1) RT(1, 1, 4, 2, 8, 2);
+    if (tok == 4) RT(4, 1, 4, 2, 8, 2);
+    if (tok == 16) RT(16, 1, 4, 2, 4, 2);
+    RT(16, 2, 4, 2, 4, 2);
   } else {
-    RT_LAUNCH_W(16, 4);
+    if (tok == 1) RT(1, 1, 4, 4, 4, 2);
+    if (tok == 4) RT(4, 1, 4, 4, 4, 2);
+    if (tok == 16) RT(16, 1, 4, 4, 2, 2);
+    RT(16, 2, 4, 4, 2, 2);
   }
-#undef RT_LAUNCH_W
-  return hipGetLastError();
+#undef RT
 }
 
 hipError_t launch_route_fwd(const moe_desc& d, const void* x, const void* wr, const float* bias, int bg,
