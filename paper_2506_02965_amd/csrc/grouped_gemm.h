@@ -1,4 +1,4 @@
-// Grouped-GEMM pieces shared by the bf16 (MFMA 16x16x32, direct-to-LDS) and fp32 kernels.
+// Grouped-GEMM pieces shared by the bf16 (MFMA 16x16x32) and fp32 (MFMA 16x16x4) kernels, both direct-to-LDS.
 #pragma once
 #include "pcmoe_internal.h"
 
@@ -41,6 +41,47 @@ template <> struct KindTraits<BWD_DH> { static constexpr bool ragged_m = true, a
 template <> struct KindTraits<BWD_DX> { static constexpr bool ragged_m = true, a_kc = true, b_kc = false; };
 template <> struct KindTraits<WG_DOWN> { static constexpr bool ragged_m = false, a_kc = false, b_kc = false; };
 template <> struct KindTraits<WG_GU> { static constexpr bool ragged_m = false, a_kc = false, b_kc = false; };
+
+typedef int int32x4 __attribute__((ext_vector_type(4)));
+
+// Buffer resource over [base, base + bytes): loads at offsets >= bytes return zeros.
+__device__ __forceinline__ int32x4 make_rsrc(const void* base, uint32_t bytes) {
+  struct {
+    const void* p;
+    uint32_t range;
+    uint32_t cfg;
+  } r = {base, bytes, 0x00020000u};
+  int32x4 v = __builtin_bit_cast(int32x4, r);
+  v.x = __builtin_amdgcn_readfirstlane(v.x);
+  v.y = __builtin_amdgcn_readfirstlane(v.y);
+  v.z = __builtin_amdgcn_readfirstlane(v.z);
+  v.w = __builtin_amdgcn_readfirstlane(v.w);
+  return v;
+}
+
+// 16 bytes per lane from the buffer at byte offset voff into LDS at lds_dst + 16 * lane. Written as
+// inline assembly on purpose: through the builtin, the compiler sees an LDS store it cannot tell apart
+// from the operand buffer being read, and waits for every outstanding load (vmcnt(0)) before the next
+// LDS read, which serialises each K-tile's load latency with the previous tile's MFMAs. Completion is
+// tracked by the explicit vmcnt waits of the main loop instead.
+__device__ __forceinline__ uint32_t lds_addr(const char* p) {
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p);
+}
+__device__ __forceinline__ void dma16(int32x4 rsrc, uint32_t m0, int voff) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %1, %2, 0 offen lds"
+      :
+      : "s"(__builtin_amdgcn_readfirstlane(m0)), "v"(voff), "s"(rsrc)
+      : "memory", "m0");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
 constexpr int GROUP_M = 8;  // m-tiles visited together for L2 reuse of the weight tiles
 
@@ -228,11 +269,12 @@ __global__ __launch_bounds__(512) void mtile_prefix_kernel(const int32_t* __rest
                                                            int32_t* __restrict__ pre2, int32_t* __restrict__ order,
                                                            int32_t* __restrict__ zero, int nzero);
 
-// fp32 path (generic LDS-tiled MFMA 16x16x4 kernel)
+// fp32 path; pre64: m-tile prefix for 64-row tiles, order: groups by decreasing row count
 hipError_t ffn_fwd_f32(const moe_desc& d, const void* x, const void* xp, const int32_t* offsets, const void* wg,
-                       const void* wu, const void* wd, void* yp, void* saved, int32_t* pre, hipStream_t s);
+                       const void* wu, const void* wd, void* yp, void* saved, const int32_t* pre64, hipStream_t s);
 hipError_t ffn_bwd_f32(const moe_desc& d, const void* x, const void* xp, const void* dy, const void* dyp,
                        const int32_t* offsets, const void* wg, const void* wu, const void* wd, const void* saved,
-                       void* dxp, void* dwg, void* dwu, void* dwd, void* dgu, int32_t* pre, hipStream_t s);
+                       void* dxp, void* dwg, void* dwu, void* dwd, void* dgu, const int32_t* pre64,
+                       const int32_t* order, hipStream_t s);
 
 }  // namespace pcmoe

@@ -33,41 +33,7 @@
 
 namespace pcmoe {
 
-typedef int int32x4 __attribute__((ext_vector_type(4)));
 typedef short short4v __attribute__((ext_vector_type(4)));
-
-// Buffer resource over [base, base + bytes): loads at offsets >= bytes return zeros.
-__device__ __forceinline__ int32x4 make_rsrc(const void* base, uint32_t bytes) {
-  struct {
-    const void* p;
-    uint32_t range;
-    uint32_t cfg;
-  } r = {base, bytes, 0x00020000u};
-  int32x4 v = __builtin_bit_cast(int32x4, r);
-  v.x = __builtin_amdgcn_readfirstlane(v.x);
-  v.y = __builtin_amdgcn_readfirstlane(v.y);
-  v.z = __builtin_amdgcn_readfirstlane(v.z);
-  v.w = __builtin_amdgcn_readfirstlane(v.w);
-  return v;
-}
-
-// 16 bytes per lane from the buffer at byte offset voff into LDS at lds_dst + 16 * lane. Written as
-// inline assembly on purpose: through the builtin, the compiler sees an LDS store it cannot tell apart
-// from the operand buffer being read, and waits for every outstanding load (vmcnt(0)) before the next
-// LDS read, which serialises each K-tile's load latency with the previous tile's MFMAs. Completion is
-// tracked by the explicit vmcnt waits of the main loop instead.
-__device__ __forceinline__ uint32_t lds_addr(const char* p) {
-  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p);
-}
-__device__ __forceinline__ void dma16(int32x4 rsrc, uint32_t m0, int voff) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %1, %2, 0 offen lds"
-      :
-      : "s"(__builtin_amdgcn_readfirstlane(m0)), "v"(voff), "s"(rsrc)
-      : "memory", "m0");
-}
 
 // K-contiguous tile rows of BK bf16 (BK = 64: 8 chunks of 16 bytes; BK = 32: 4 chunks): chunk c of row r
 // lives at chunk c ^ kc_swz(r). With the two 8-byte halves read by alternating lane groups, 16 rows of
@@ -147,12 +113,6 @@ __device__ __forceinline__ void mfma_bf16(floatx4& acc, const Chunk& a, const Ch
 // Logistic sigmoid for epilogues whose results are rounded to bf16: hardware exp and reciprocal (about
 // 1 ulp of fp32 each) instead of an IEEE division; saturates to 0 and 1 at the tails.
 __device__ __forceinline__ float sigmoid_bf16_out(float x) { return __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 
 template <int BM, int BN, int BK, int STAGES, int WM, int WN>
 struct Cfg2 {
@@ -1160,7 +1120,7 @@ size_t ffn_bwd_ws_bytes(const moe_desc& d) {
 }
 
 struct Plan {
-  int32_t* pre128;
+  int32_t* pre128;   // fp32 layers: for 64-row tiles
   int32_t* pre256;
   int32_t* order;
   int32_t* body256;  // 256-row m-tiles other than the tails
@@ -1185,8 +1145,9 @@ static Plan plan(const moe_desc& d, const int32_t* offsets, void* where, hipStre
                  int nzero = 0) {
   Plan pl = plan_at(d, where);
   KernelTimer kt("ffn_plan", s);
-  hipLaunchKernelGGL(mtile_prefix_kernel, dim3(1), dim3(512), 0, s, offsets, d.local_count, d.n_shared, d.T, 128, 256,
-                     192, pl.pre128, pl.pre256, pl.body256, pl.tail256, pl.pre192, pl.order, zero, nzero);
+  hipLaunchKernelGGL(mtile_prefix_kernel, dim3(1), dim3(512), 0, s, offsets, d.local_count, d.n_shared, d.T,
+                     d.dtype == MOE_BF16 ? 128 : 64, 256, 192, pl.pre128, pl.pre256, pl.body256, pl.tail256, pl.pre192,
+                     pl.order, zero, nzero);
   return pl;
 }
 
@@ -1350,7 +1311,7 @@ hipError_t launch_ffn_bwd(const moe_desc& d, const void* x, const void* xp, cons
   (void)es;
   Plan pl = plan_at(d, (char*)saved + saved_plan_offset(d));  // written by the forward for the same offsets
   if (d.dtype != MOE_BF16)
-    return ffn_bwd_f32(d, x, xp, dy, dyp, offsets, wg, wu, wd, saved, dxp, dwg, dwu, dwd, dgu, pl.pre128, s);
+    return ffn_bwd_f32(d, x, xp, dy, dyp, offsets, wg, wu, wd, saved, dxp, dwg, dwu, dwd, dgu, pl.pre128, pl.order, s);
   GemmArgs a = args_for(d, offsets);
   a.x = x; a.xp = xp; a.dy = dy; a.dyp = dyp; a.wg = wg; a.wu = wu; a.wd = wd;
   a.gu = (void*)saved;

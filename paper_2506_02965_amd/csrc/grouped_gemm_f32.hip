@@ -1,5 +1,5 @@
 // Expert passes of Alg. 6 (ForwardExpert / BackwardExpert) as grouped GEMMs — fp32 storage path
-// (v_mfma_f32_16x16x4_f32, register-staged double buffer). The bf16 path is grouped_gemm_bf16.hip.
+// (v_mfma_f32_16x16x4_f32). The bf16 path is grouped_gemm_bf16.hip.
 //
 // One kernel template covers the six contractions of a SwiGLU expert:
 //   FWD_GU   [G|U] = h W_{gate|up}^T, epilogue H = silu(G) * U    (M = rows, N = 2f, K = d)
@@ -9,352 +9,268 @@
 //   WG_DOWN  dW_down = dO^T H                                      (M = d,  N = f,  K = rows)
 //   WG_GU    [dW_gate;dW_up] = [dG|dU]^T h                         (M = 2f, N = d,  K = rows)
 // Groups are the hosted routed experts (rows from the dispatch offsets, read on the device) and
-// the shared experts (all T tokens). Tiles: BM x BN per workgroup of 2x2 wavefronts, K staged in
-// LDS 128 bytes per row (64 bf16 / 32 fp32) with a 16-byte-chunk XOR swizzle, double-buffered,
-// fp32 accumulation in MFMA registers (bf16: v_mfma_f32_16x16x32_bf16, fp32: v_mfma_f32_16x16x4_f32).
-// Operands whose K dimension is not contiguous in memory are transposed in registers on their
-// way to LDS (8x8 blocks of bf16 / 4x4 of fp32), so the MFMA side always reads K-contiguous rows.
-// Epilogues stage the fp32 tile through LDS and write 16-byte chunks.
+// the shared experts (all T tokens).
+//
+// What bounds it: the fp32 matrix rate (154 TFLOP/s measured; a 16x16x4 MFMA takes 32 cycles), so operand traffic is
+// cheap and the design spends it on balance and on wavefronts in flight: 64 x 64 tiles of 4 wavefronts, four
+// workgroups per CU. Measured on T = 1500, d = 512, f = 1024, E = 8, top-2, one shared expert (forward and backward,
+// 43 GFLOP): 481 us against 494 with three stages (three workgroups per CU), 526 with 128 x 64 tiles and 697 with
+// 128 x 128 ones (1,240 before); the order is the same at 6,000 rows of d = 1024 (119 TFLOP/s) and at 10 rows.
+// Operands stream global -> LDS through direct loads into a two-stage ring of 32-deep K-tiles; rows past a group's
+// end read as zeros through the buffer range check. Both operand layouts are kept as they lie in memory: K-contiguous
+// rows are read as 16-byte chunks (lane group q holds k = 4q .. 4q + 3 and feeds four MFMAs), K-major rows word by
+// word at the same k, so nothing is transposed. The MFMAs multiply B by A, which leaves four consecutive output columns in a lane: the
+// epilogue stores 16 bytes straight from the accumulators. The backward runs each weight gradient in one launch with
+// an independent input gradient.
 #include "grouped_gemm.h"
 
 namespace pcmoe {
 
-__device__ __forceinline__ int swz(int r) { return ((r >> 1) ^ (r >> 4)) & 7; }
-__device__ __forceinline__ int lds_off(int r, int c) { return r * 128 + ((c ^ swz(r)) << 4); }
-
-template <typename T> struct Mfma;
-template <> struct Mfma<bf16> {
-  static __device__ __forceinline__ void run(floatx4& acc, const Chunk& a, const Chunk& b) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
-                                                  0, 0, 0);
-  }
+struct CfgF {
+  static constexpr int BM = 64, BN = 64, STAGES = 2;
+  static constexpr int BK = 32, ROWB = 128;  // K-tile depth; bytes of a K-contiguous tile row (8 chunks)
+  static constexpr int NW = 4, NT = 256;     // 2 x 2 wavefronts
+  static constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16;
+  // 1 KB per direct load: 8 K-contiguous rows or 4 K-major rows. K-major blocks are followed by 64 bytes of padding,
+  // which puts the rows of lane groups q = 0 .. 3 (four rows apart) 16 banks apart.
+  static constexpr int IA = BM * ROWB / 1024, IB = BN * ROWB / 1024;
+  static constexpr int KM_BLOCK = 1024 + 64;
+  static constexpr int A_BYTES = IA * KM_BLOCK;
+  static constexpr int STAGE = A_BYTES + IB * KM_BLOCK;
+  static constexpr int LDS = STAGES * STAGE;
+  static constexpr int LA = IA / NW, LB = IB / NW, LOADS = LA + LB;
 };
-template <> struct Mfma<float> {
-  static __device__ __forceinline__ void run(floatx4& acc, const Chunk& a, const Chunk& b) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w[i]), __uint_as_float(b.w[i]), acc, 0, 0, 0);
-  }
-};
+typedef CfgF C;
 
-// Transpose an EPC x EPC block held as EPC chunks (row i = chunk i) so that out[m] holds column m.
-__device__ __forceinline__ void transpose_block(const Chunk* in, Chunk* out, bf16) {
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t lo = in[2 * j].w[m >> 1], hi = in[2 * j + 1].w[m >> 1];
-      out[m].w[j] = (m & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
-    }
-  }
-}
-__device__ __forceinline__ void transpose_block(const Chunk* in, Chunk* out, float) {
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) out[m].w[j] = in[j].w[m];
-}
+// 16-byte chunk c of K-contiguous tile row r lies at slot c ^ f_swz(r).
+__device__ __forceinline__ int f_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
-template <typename T, int BM, int BN, int WM, int WN>
-struct TileCfg {
-  static constexpr int NT = 64 * WM * WN;
-  static constexpr int EPCN = EPC<T>::value;
-  static constexpr int BK = 8 * EPCN;              // elements per 128-byte LDS row
-  static constexpr int WTM = BM / WM, WTN = BN / WN;
-  static constexpr int FM = WTM / 16, FN = WTN / 16;
-  static constexpr int CP = BN + 16;               // fp32 pitch of the epilogue tile
-  static constexpr int LDS_MAIN = 2 * (BM + BN) * 128;
-  static constexpr int LDS_EPI = BM * CP * 4;
-  static constexpr int LDS = LDS_MAIN > LDS_EPI ? LDS_MAIN : LDS_EPI;
-};
-
-// Loader of a K-contiguous operand tile: R rows x 8 chunks, NT threads.
-template <int R, int NT>
-struct KcLoader {
-  static constexpr int N = (R * 8 + NT - 1) / NT;
-  const char* src[N];
-  int off[N];
-  Chunk reg[N];
-  __device__ __forceinline__ void load(int kbyte) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) reg[i] = src[i] ? ld_chunk(src[i] + kbyte) : zero_chunk();
-  }
-  __device__ __forceinline__ void store(char* lds) {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      if (off[i] >= 0) st_chunk(lds + off[i], reg[i]);
-  }
-};
-
-// Loader of an MN-contiguous operand tile (K rows in memory, R contiguous columns): EPC x EPC
-// blocks, transposed in registers.
-template <typename T, int R, int NT>
-struct McLoader {
-  static constexpr int E = EPC<T>::value;
-  static constexpr int NBLK = 8 * (R / E);
-  static constexpr int N = (NBLK + NT - 1) / NT;
-  const char* src[N];   // column base of the block (row 0 of the tile), or null
-  int kb[N];            // k-block (chunk index in LDS)
-  int mb[N];            // mn-block
-  Chunk reg[N][E];
-  __device__ __forceinline__ void load(ptrdiff_t shift, int ld_bytes, int krow0, int kvalid) {
-    // shift: byte offset added to src (selects the K-tile's source half); krow0: first K row
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-#pragma unroll
-      for (int r = 0; r < E; ++r) {
-        const int kr = krow0 + kb[i] * E + r;
-        reg[i][r] = (src[i] && kr < kvalid) ? ld_chunk(src[i] + shift + (size_t)kr * ld_bytes)
-                                            : zero_chunk();
-      }
-    }
-  }
-  __device__ __forceinline__ void store(char* lds) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      if (kb[i] < 0) continue;
-      Chunk tr[E];
-      transpose_block(reg[i], tr, T());
-      const int par = mb[i] & 1;
-#pragma unroll
-      for (int r = 0; r < E; ++r) {
-        const int rr = r ^ par;  // alternate the row order of odd blocks: spreads LDS banks
-        Chunk v;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v.w[q] = par ? tr[r ^ 1].w[q] : tr[r].w[q];
-        st_chunk(lds + lds_off(mb[i] * E + rr, kb[i]), v);
-      }
-    }
-  }
-};
-
-template <typename T, int BM, int BN, int WM, int WN, int KIND>
-__global__ __launch_bounds__(64 * WM * WN) void grouped_gemm_kernel(GemmArgs p) {
-  using C = TileCfg<T, BM, BN, WM, WN>;
+template <int KIND>
+__device__ __forceinline__ void gemm_tile_f32(const GemmArgs& p, int bid, char* smem) {
   using KT = KindTraits<KIND>;
-  constexpr int NT = C::NT, E = C::EPCN, BK = C::BK;
-  extern __shared__ __align__(16) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  constexpr int ES = 4, BM = C::BM, BN = C::BN, BK = C::BK, NW = C::NW;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int li = lane & 15, q = lane >> 4;
 
-  // ---------------------------------------------------------------- tile decode
   TileIdx ti;
-  if (!decode_tile<KT::ragged_m>(p, blockIdx.x, ti)) return;
-  const int g = ti.g, mt = ti.mt, nt = ti.nt;
-
+  if (!decode_tile<KT::ragged_m>(p, bid, ti)) return;
+  const int g = ti.g, d = p.d, f = p.f;
   const bool routed = g < p.Eloc;
-  const int row0 = ti.row0;                                          // first row of the group in its source
-  const int rows = ti.rows;                                          // rows of the group
-  const size_t rs = routed ? (size_t)row0 : (size_t)p.rows_cap + (size_t)(g - p.Eloc) * p.T;  // row-space base
-  const int d = p.d, f = p.f;
-  const size_t es = sizeof(T);
-
-  const int m0 = mt * BM, n0 = nt * BN;
+  const int rows = ti.rows;
+  const size_t rs = routed ? (size_t)ti.row0 : (size_t)p.rows_cap + (size_t)(g - p.Eloc) * p.T;  // row-space base
+  const int m0 = ti.mt * BM, n0 = ti.nt * BN;
   int K;
   if (KIND == FWD_GU || KIND == BWD_DH) K = d;
   else if (KIND == FWD_DOWN) K = f;
   else if (KIND == BWD_DX) K = 2 * f;
   else K = rows;
 
-  // ------------------------------------------------------------- operand setup
-  KcLoader<BM, NT> akc;
-  KcLoader<BN, NT> bkc;
-  McLoader<T, BM, NT> amc;
-  McLoader<T, BN, NT> bmc;
-  int a_ld = 0, b_ld = 0;          // bytes
-  ptrdiff_t b_half_shift = 0;      // BWD_DX: added to W_gate addresses for K rows >= f (W_up)
+  // ------------------------------------------------------------------ operand sources (as in the bf16 kernel)
+  const char *a_base, *b0_base, *b1_base;
+  uint32_t b_bytes;
+  int a_ld, b_ld;
+  if (KIND == FWD_GU) { a_base = routed ? (const char*)p.xp + rs * d * ES : (const char*)p.x; a_ld = d * ES; }
+  else if (KIND == FWD_DOWN) { a_base = (const char*)p.h + rs * f * ES; a_ld = f * ES; }
+  else if (KIND == BWD_DH || KIND == WG_DOWN) {
+    a_base = routed ? (const char*)p.dyp + rs * d * ES : (const char*)p.dy;
+    a_ld = d * ES;
+  } else { a_base = (const char*)p.dgu + rs * 2 * f * ES; a_ld = 2 * f * ES; }
+  if (KIND == FWD_GU || KIND == BWD_DX) {
+    b0_base = (const char*)p.wg + (size_t)g * f * d * ES;
+    b1_base = (const char*)p.wu + (size_t)g * f * d * ES;
+    b_bytes = (uint32_t)((size_t)f * d * ES);
+    b_ld = d * ES;
+  } else if (KIND == FWD_DOWN || KIND == BWD_DH) {
+    b0_base = b1_base = (const char*)p.wd + (size_t)g * d * f * ES;
+    b_bytes = (uint32_t)((size_t)d * f * ES);
+    b_ld = f * ES;
+  } else if (KIND == WG_DOWN) {
+    b0_base = b1_base = (const char*)p.h + rs * f * ES;
+    b_bytes = (uint32_t)((size_t)rows * f * ES);
+    b_ld = f * ES;
+  } else {  // WG_GU
+    b0_base = b1_base = routed ? (const char*)p.xp + rs * d * ES : (const char*)p.x;
+    b_bytes = (uint32_t)((size_t)rows * d * ES);
+    b_ld = d * ES;
+  }
+  const int32x4 ra = make_rsrc(a_base, (uint32_t)((size_t)rows * a_ld)), rb0 = make_rsrc(b0_base, b_bytes),
+                rb1 = make_rsrc(b1_base, b_bytes);
 
-  if (KT::a_kc) {
-    const char* abase;
-    if (KIND == FWD_GU) { abase = routed ? (const char*)p.xp + rs * d * es : (const char*)p.x; a_ld = d * es; }
-    else if (KIND == FWD_DOWN) { abase = (const char*)p.h + rs * f * es; a_ld = f * es; }
-    else if (KIND == BWD_DH) { abase = routed ? (const char*)p.dyp + rs * d * es : (const char*)p.dy; a_ld = d * es; }
-    else { abase = (const char*)p.dgu + rs * 2 * f * es; a_ld = 2 * f * es; }
+  // Per-lane byte offset at K-tile 0 of this wavefront's direct loads jj = wave + 4 j of each operand.
+  int va[C::LA], vb[C::LB];
+  bool bup[C::LB];
 #pragma unroll
-    for (int i = 0; i < KcLoader<BM, NT>::N; ++i) {
-      const int q = tid + i * NT;
-      const int r = q >> 3, c = q & 7;
-      const bool in_tile = r < BM;
-      akc.off[i] = in_tile ? lds_off(r, c) : -1;
-      akc.src[i] = (in_tile && m0 + r < rows) ? abase + (size_t)(m0 + r) * a_ld + c * 16 : nullptr;
-    }
-  } else {
-    const char* abase;  // [K rows][M cols] with M contiguous
-    if (KIND == WG_DOWN) { abase = routed ? (const char*)p.dyp + rs * d * es : (const char*)p.dy; a_ld = d * es; }
-    else { abase = (const char*)p.dgu + rs * 2 * f * es; a_ld = 2 * f * es; }
-#pragma unroll
-    for (int i = 0; i < McLoader<T, BM, NT>::N; ++i) {
-      const int blk = tid + i * NT;
-      const bool ok = blk < McLoader<T, BM, NT>::NBLK;
-      const int nmb = BM / E;
-      amc.kb[i] = ok ? blk / nmb : -1;
-      amc.mb[i] = ok ? blk % nmb : 0;
-      amc.src[i] = ok ? abase + (size_t)(m0 + amc.mb[i] * E) * es : nullptr;
+  for (int j = 0; j < C::LA; ++j) {
+    const int jj = wave + NW * j;
+    if (KT::a_kc) {
+      const int r = 8 * jj + (lane >> 3), c = (lane & 7) ^ f_swz(r);
+      va[j] = (m0 + r) * a_ld + 16 * c;
+    } else {
+      constexpr int CPR = BM / 4;  // chunks per K-major row
+      const int slot = 64 * jj + lane;
+      va[j] = (slot / CPR) * a_ld + (m0 + 4 * (slot % CPR)) * ES;
     }
   }
-  if (KT::b_kc) {
 #pragma unroll
-    for (int i = 0; i < KcLoader<BN, NT>::N; ++i) {
-      const int q = tid + i * NT;
-      const int r = q >> 3, c = q & 7;
-      const bool in_tile = r < BN;
-      bkc.off[i] = in_tile ? lds_off(r, c) : -1;
-      const char* src = nullptr;
-      if (in_tile) {
-        if (KIND == FWD_GU) {
-          // LDS row r: wave column r / WTN; its first half are gate rows, the second half up rows
-          const int wcol = r / C::WTN, within = r % C::WTN, half = C::WTN / 2;
-          const int frow = nt * (BN / 2) + wcol * half + (within % half);
-          const char* wsrc = (within < half) ? (const char*)p.wg : (const char*)p.wu;
-          src = wsrc + ((size_t)g * f * d + (size_t)frow * d) * es + c * 16;
-          b_ld = d * es;
-        } else {  // FWD_DOWN: W_down[g] rows = output columns, K = f contiguous
-          src = (const char*)p.wd + ((size_t)g * d * f + (size_t)(n0 + r) * f) * es + c * 16;
-          b_ld = f * es;
-        }
+  for (int j = 0; j < C::LB; ++j) {
+    const int jj = wave + NW * j;
+    bup[j] = false;
+    if (KT::b_kc) {
+      const int r = 8 * jj + (lane >> 3), c = (lane & 7) ^ f_swz(r);
+      int wrow = n0 + r;
+      if (KIND == FWD_GU) {  // wave column: its first WTN / 2 rows are gate rows, the others the same up rows
+        constexpr int HALF = C::WTN / 2;
+        const int within = r % C::WTN;
+        wrow = ti.nt * (BN / 2) + (r / C::WTN) * HALF + within % HALF;
+        bup[j] = (8 * jj) % C::WTN >= HALF;  // the load's 8 rows are all gate or all up rows
       }
-      bkc.src[i] = src;
-    }
-  } else {
-    const char* bbase;  // [K rows][N cols] with N contiguous, column n0
-    if (KIND == BWD_DH) { bbase = (const char*)p.wd + (size_t)g * d * f * es; b_ld = f * es; }
-    else if (KIND == BWD_DX) {
-      bbase = (const char*)p.wg + (size_t)g * f * d * es;
-      b_ld = d * es;
-      b_half_shift = ((const char*)p.wu - (const char*)p.wg) - (ptrdiff_t)f * d * es;
-    } else if (KIND == WG_DOWN) { bbase = (const char*)p.h + rs * f * es; b_ld = f * es; }
-    else { bbase = routed ? (const char*)p.xp + rs * d * es : (const char*)p.x; b_ld = d * es; }
-#pragma unroll
-    for (int i = 0; i < McLoader<T, BN, NT>::N; ++i) {
-      // B blocks start at the other half of the workgroup when A also needs the transposing loader
-      const int tb = KT::a_kc ? tid : (tid + NT / 2) % NT;
-      const int blk = tb + i * NT;
-      const bool ok = blk < McLoader<T, BN, NT>::NBLK;
-      const int nmb = BN / E;
-      bmc.kb[i] = ok ? blk / nmb : -1;
-      bmc.mb[i] = ok ? blk % nmb : 0;
-      bmc.src[i] = ok ? bbase + (size_t)(n0 + bmc.mb[i] * E) * es : nullptr;
+      vb[j] = wrow * b_ld + 16 * c;
+    } else {
+      constexpr int CPR = BN / 4;
+      const int slot = 64 * jj + lane;
+      vb[j] = (slot / CPR) * b_ld + (n0 + 4 * (slot % CPR)) * ES;
     }
   }
+  const uint32_t lds_base = lds_addr(smem);
+  const auto issue = [&](int kt, int stage) {
+    const int k0 = kt * BK;
+    const uint32_t st = lds_base + stage * C::STAGE;
+#pragma unroll
+    for (int j = 0; j < C::LA; ++j) {
+      const int jj = wave + NW * j;
+      dma16(ra, st + jj * (KT::a_kc ? 1024 : C::KM_BLOCK), va[j] + (KT::a_kc ? k0 * ES : k0 * a_ld));
+    }
+#pragma unroll
+    for (int j = 0; j < C::LB; ++j) {
+      const int jj = wave + NW * j;
+      const uint32_t dst = st + C::A_BYTES + jj * (KT::b_kc ? 1024 : C::KM_BLOCK);
+      if (KIND == BWD_DX) {
+        const bool hi = k0 >= f;  // K rows >= f are W_up rows
+        dma16(hi ? rb1 : rb0, dst, vb[j] + (hi ? k0 - f : k0) * b_ld);
+      } else {
+        dma16(bup[j] ? rb1 : rb0, dst, vb[j] + (KT::b_kc ? k0 * ES : k0 * b_ld));
+      }
+    }
+  };
 
-  // ---------------------------------------------------------------- main loop
   floatx4 acc[C::FM][C::FN];
 #pragma unroll
   for (int i = 0; i < C::FM; ++i)
 #pragma unroll
     for (int j = 0; j < C::FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  const int KT_N = (K + BK - 1) / BK;
-  auto load_tile = [&](int kt) {
-    const int k0 = kt * BK;
-    if (KT::a_kc) akc.load(k0 * es);
-    else amc.load(0, a_ld, k0, K);
-    if (KT::b_kc) bkc.load(k0 * es);
-    else bmc.load((KIND == BWD_DX && k0 >= f) ? b_half_shift : 0, b_ld, k0, K);
-  };
-  auto store_tile = [&](int buf) {
-    char* As = smem + buf * (BM + BN) * 128;
-    char* Bs = As + BM * 128;
-    if (KT::a_kc) akc.store(As);
-    else amc.store(As);
-    if (KT::b_kc) bkc.store(Bs);
-    else bmc.store(Bs);
-  };
-
-  if (KT_N > 0) {
-    load_tile(0);
-    store_tile(0);
-  }
-  __syncthreads();
-  const int frow = lane & 15, fchunk = lane >> 4;
-  for (int kt = 0; kt < KT_N; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < KT_N) load_tile(kt + 1);
-    const char* As = smem + buf * (BM + BN) * 128;
-    const char* Bs = As + BM * 128;
+  // Fragment i (16 rows) of 16-deep step kk: element s is row (or column) 16 i + li at k = 16 kk + 4 q + s.
+  const auto frag = [&](const char* S, auto kc, int w0, int kk, int i, float (&v)[4]) {
+    if constexpr (decltype(kc)::value) {
+      const int r = w0 + 16 * i + li;
+      const Chunk c = ld_chunk(S + r * C::ROWB + (((4 * kk + q) ^ f_swz(r)) << 4));
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      Chunk a[C::FM], b[C::FN];
+      for (int s = 0; s < 4; ++s) v[s] = __uint_as_float(c.w[s]);
+    } else {
 #pragma unroll
-      for (int i = 0; i < C::FM; ++i) a[i] = ld_chunk(As + lds_off(wm * C::WTM + 16 * i + frow, 4 * kk + fchunk));
-#pragma unroll
-      for (int j = 0; j < C::FN; ++j) b[j] = ld_chunk(Bs + lds_off(wn * C::WTN + 16 * j + frow, 4 * kk + fchunk));
-#pragma unroll
-      for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) Mfma<T>::run(acc[i][j], a[i], b[j]);
+      for (int s = 0; s < 4; ++s) {
+        const int k = 16 * kk + 4 * q + s;
+        v[s] = *reinterpret_cast<const float*>(S + (k / 4) * C::KM_BLOCK + (k % 4) * 256 + (w0 + 16 * i + li) * 4);
+      }
     }
-    if (kt + 1 < KT_N) store_tile(buf ^ 1);
-    __syncthreads();
+  };
+  const int KTN = (K + BK - 1) / BK;
+  const bool wave_rows = !KT::ragged_m || m0 + wm * C::WTM < rows;  // wave-uniform
+#pragma unroll
+  for (int s = 0; s < C::STAGES - 1; ++s)
+    if (s < KTN) issue(s, s);
+  int stage = 0, fill = C::STAGES - 1;
+  for (int kt = 0; kt < KTN; ++kt) {
+    // K-tile kt has landed when at most the later tiles' loads are outstanding
+    if (kt + C::STAGES - 2 < KTN) wait_vmcnt<(C::STAGES - 2) * C::LOADS>();
+    else wait_vmcnt<0>();
+    // every wave's loads of kt have landed, and its reads of the stage about to be refilled are done
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (kt + C::STAGES - 1 < KTN) issue(kt + C::STAGES - 1, fill);
+    const char* As = smem + stage * C::STAGE;
+    const char* Bs = As + C::A_BYTES;
+    stage = stage + 1 == C::STAGES ? 0 : stage + 1;
+    fill = fill + 1 == C::STAGES ? 0 : fill + 1;
+    if (!wave_rows) continue;  // all rows lie past the group's end: only loads and syncs
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk) {
+      float a[C::FM][4], b[C::FN][4];
+#pragma unroll
+      for (int i = 0; i < C::FM; ++i) frag(As, std::bool_constant<KT::a_kc>{}, wm * C::WTM, kk, i, a[i]);
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j) frag(Bs, std::bool_constant<KT::b_kc>{}, wn * C::WTN, kk, j, b[j]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+          for (int j = 0; j < C::FN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][s], a[i][s], acc[i][j], 0, 0, 0);
+    }
   }
 
-  // ---------------------------------------------------------------- epilogue
-  float* Cs = reinterpret_cast<float*>(smem);
+  // ------------------------------------------------------------------ epilogue: lane (li, q) of block (i, j) holds
+  // row 16 i + li, columns 16 j + 4 q .. + 3
 #pragma unroll
   for (int i = 0; i < C::FM; ++i) {
+    const int m = m0 + wm * C::WTM + 16 * i + li;
+    if (KT::ragged_m && m >= rows) continue;
+    if (KIND == FWD_GU) {
+#pragma unroll
+      for (int j = 0; j < C::FN / 2; ++j) {
+        const floatx4 gv = acc[i][j], uv = acc[i][j + C::FN / 2];
+        floatx4 hv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float sg = 1.f / (1.f + __expf(-gv[e]));
+          hv[e] = gv[e] * sg * uv[e];
+        }
+        const int col = ti.nt * (BN / 2) + wn * (C::WTN / 2) + 16 * j + 4 * q;
+        float* gu = (float*)p.gu + (rs + m) * 2 * f + col;
+        *reinterpret_cast<floatx4*>(gu) = gv;
+        *reinterpret_cast<floatx4*>(gu + f) = uv;
+        *reinterpret_cast<floatx4*>((float*)p.h + (rs + m) * f + col) = hv;
+      }
+      continue;
+    }
 #pragma unroll
     for (int j = 0; j < C::FN; ++j) {
-      int col;
-      if (KIND == FWD_GU) {
-        const int half = C::FN / 2;
-        col = (j < half) ? wn * (C::WTN / 2) + 16 * j + frow
-                         : BN / 2 + wn * (C::WTN / 2) + 16 * (j - half) + frow;
-      } else {
-        col = wn * C::WTN + 16 * j + frow;
-      }
+      const floatx4 v = acc[i][j];
+      const int col = n0 + wn * C::WTN + 16 * j + 4 * q;
+      if (KIND == FWD_DOWN || KIND == BWD_DX) {
+        *reinterpret_cast<floatx4*>((float*)p.out + (rs + m) * d + col) = v;
+      } else if (KIND == BWD_DH) {
+        const float* gu = (const float*)p.gu + (rs + m) * 2 * f + col;
+        const floatx4 gv = *reinterpret_cast<const floatx4*>(gu), uv = *reinterpret_cast<const floatx4*>(gu + f);
+        floatx4 dg, du;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Cs[(wm * C::WTM + 16 * i + 4 * fchunk + r) * C::CP + col] = acc[i][j][r];
+        for (int e = 0; e < 4; ++e) {
+          const float sg = 1.f / (1.f + __expf(-gv[e]));
+          du[e] = v[e] * gv[e] * sg;
+          dg[e] = v[e] * uv[e] * sg * (1.f + gv[e] * (1.f - sg));
+        }
+        float* o = (float*)p.dgu + (rs + m) * 2 * f + col;
+        *reinterpret_cast<floatx4*>(o) = dg;
+        *reinterpret_cast<floatx4*>(o + f) = du;
+      } else if (KIND == WG_DOWN) {
+        *reinterpret_cast<floatx4*>((float*)p.out + ((size_t)g * d + m) * f + col) = v;
+      } else {  // WG_GU
+        float* o = m < f ? (float*)p.out + ((size_t)g * f + m) * d + col
+                         : (float*)p.out2 + ((size_t)g * f + (m - f)) * d + col;
+        *reinterpret_cast<floatx4*>(o) = v;
+      }
     }
   }
-  __syncthreads();
+}
 
-  constexpr int OUT_COLS = (KIND == FWD_GU) ? BN / 2 : BN;
-  constexpr int CPR = OUT_COLS / E;  // output chunks per tile row
-  for (int q = tid; q < BM * CPR; q += NT) {
-    const int r = q / CPR, c = q % CPR;
-    const int m = m0 + r;
-    if (KT::ragged_m && m >= rows) continue;
-    float v[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = Cs[r * C::CP + c * E + e];
-    if (KIND == FWD_GU) {
-      float u[E], hv[E];
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        u[e] = Cs[r * C::CP + BN / 2 + c * E + e];
-        const float sg = 1.f / (1.f + __expf(-v[e]));
-        hv[e] = v[e] * sg * u[e];
-      }
-      const int col = nt * (BN / 2) + c * E;
-      char* gu = (char*)p.gu + ((rs + m) * 2 * f + col) * es;
-      st_chunk(gu, f_to_chunk<T>(v));
-      st_chunk(gu + (size_t)f * es, f_to_chunk<T>(u));
-      st_chunk((char*)p.h + ((rs + m) * f + col) * es, f_to_chunk<T>(hv));
-    } else if (KIND == FWD_DOWN || KIND == BWD_DX) {
-      st_chunk((char*)p.out + ((rs + m) * d + n0 + c * E) * es, f_to_chunk<T>(v));
-    } else if (KIND == BWD_DH) {
-      const int col = n0 + c * E;
-      const char* gu = (const char*)p.gu + ((rs + m) * 2 * f + col) * es;
-      float gv[E], uv[E], dg[E], du[E];
-      chunk_to_f<T>(ld_chunk(gu), gv);
-      chunk_to_f<T>(ld_chunk(gu + (size_t)f * es), uv);
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const float sg = 1.f / (1.f + __expf(-gv[e]));
-        du[e] = v[e] * gv[e] * sg;
-        dg[e] = v[e] * uv[e] * sg * (1.f + gv[e] * (1.f - sg));
-      }
-      char* o = (char*)p.dgu + ((rs + m) * 2 * f + col) * es;
-      st_chunk(o, f_to_chunk<T>(dg));
-      st_chunk(o + (size_t)f * es, f_to_chunk<T>(du));
-    } else if (KIND == WG_DOWN) {
-      st_chunk((char*)p.out + (((size_t)g * d + m) * f + n0 + c * E) * es, f_to_chunk<T>(v));
-    } else {  // WG_GU
-      char* o = (m < f) ? (char*)p.out + (((size_t)g * f + m) * d + n0 + c * E) * es
-                        : (char*)p.out2 + (((size_t)g * f + (m - f)) * d + n0 + c * E) * es;
-      st_chunk(o, f_to_chunk<T>(v));
-    }
-  }
+// Workgroups [0, grid_a) take tiles of KA, the others tiles of KB (independent contractions).
+template <int KA, int KB>
+__global__ __launch_bounds__(C::NT) void gemm_f32_kernel(GemmArgs pa, GemmArgs pb, int grid_a) {
+  extern __shared__ __align__(16) char smem[];
+  const int bid = blockIdx.x;
+  if (KA == KB || bid < grid_a) gemm_tile_f32<KA>(pa, bid, smem);
+  else gemm_tile_f32<KB>(pb, bid - grid_a, smem);
 }
 
 // m-tile prefixes over groups for two tile heights: pre[g] = sum_{g' < g} ceil(rows_g' / bm); and
@@ -417,86 +333,80 @@ __global__ __launch_bounds__(512) void mtile_prefix_kernel(const int32_t* __rest
 
 // ------------------------------------------------------------------------- host side
 
-constexpr int T_BM = 128, T_BN = 128, T_WM = 2, T_WN = 2;
+static int round8(long v) { return (int)((v + 7) / 8 * 8); }
 
-template <typename T, int KIND>
-static hipError_t run_gemm(const GemmArgs& a, int grid, hipStream_t s, const char* name) {
-  using Cf = TileCfg<T, T_BM, T_BN, T_WM, T_WN>;
-  auto kern = grouped_gemm_kernel<T, T_BM, T_BN, T_WM, T_WN, KIND>;
-  static std::atomic<uint64_t> lds_set{0};
-  if (hipError_t e = lds_limit_once((const void*)kern, Cf::LDS, lds_set); e != hipSuccess) return e;
+template <int KA, int KB>
+static hipError_t run_f32(const GemmArgs& a, long tiles_a, const GemmArgs& b, long tiles_b, hipStream_t s,
+                          const char* name) {
+  auto kern = gemm_f32_kernel<KA, KB>;
+  static_assert(C::LDS <= 65536, "more LDS needs the kernel's limit raised");
+  const int grid_a = round8(tiles_a), grid = grid_a + (KA == KB ? 0 : round8(tiles_b));
   if (grid <= 0) return hipSuccess;
   KernelTimer kt(name, s);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(Cf::NT), Cf::LDS, s, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(C::NT), C::LDS, s, a, b, grid_a);
   return hipGetLastError();
 }
 
-static int round8(long v) { return (int)((v + 7) / 8 * 8); }
-
-// Upper bound on the m-tiles of the row-ragged kinds (per-expert counts stay on the device).
-static long mtile_bound(const moe_desc& d) {
-  long routed = ((long)d.T * d.top_k + (long)d.local_count * (T_BM - 1)) / T_BM;
-  return routed + (long)d.n_shared * ((d.T + T_BM - 1) / T_BM);
-}
-
-static GemmArgs base_args(const moe_desc& d, const int32_t* offsets, const int32_t* pre) {
+static GemmArgs base_args(const moe_desc& d, const int32_t* offsets) {
   GemmArgs a{};
   a.T = d.T; a.k = d.top_k; a.d = d.d_model; a.f = d.d_ff; a.Eloc = d.local_count; a.S = d.n_shared;
   a.rows_cap = d.T * d.top_k;
   a.offsets = offsets;
-  a.mt_prefix = pre;
   return a;
 }
 
-// pre: m-tile prefix for 128-row tiles (computed by the caller's plan launch)
+// Workgroups of a contraction with `cols` output columns: row-ragged kinds (an upper bound on their m-tiles, since the
+// per-expert counts stay on the device) and weight gradients.
+static long ragged_tiles(const moe_desc& d, GemmArgs& a, int cols) {
+  a.n_tiles = cols / C::BN;
+  const long m_tiles = ((long)d.T * d.top_k + (long)d.local_count * (C::BM - 1)) / C::BM +
+                       (long)d.n_shared * ((d.T + C::BM - 1) / C::BM);
+  return m_tiles * a.n_tiles;
+}
+static long wgrad_tiles(const moe_desc& d, GemmArgs& a, int M, int N) {
+  a.m_tiles = M / C::BM;
+  a.n_tiles = N / C::BN;
+  return (long)(d.local_count + d.n_shared) * a.m_tiles * a.n_tiles;
+}
+
 hipError_t ffn_fwd_f32(const moe_desc& d, const void* x, const void* xp, const int32_t* offsets, const void* wg,
-                       const void* wu, const void* wd, void* yp, void* saved, int32_t* pre, hipStream_t s) {
-  using T = float;
-  const size_t R = (size_t)rows_total(d), es = sizeof(T);
-  GemmArgs a = base_args(d, offsets, pre);
+                       const void* wu, const void* wd, void* yp, void* saved, const int32_t* pre64, hipStream_t s) {
+  const size_t R = (size_t)rows_total(d), es = sizeof(float);
+  GemmArgs a = base_args(d, offsets);
   a.x = x; a.xp = xp; a.wg = wg; a.wu = wu; a.wd = wd;
   a.gu = saved;
   a.h = (char*)saved + align256(R * 2 * d.d_ff * es);
   a.out = yp;
-  const long mtb = mtile_bound(d);
-  hipError_t e;
-  a.n_tiles = d.d_ff / (T_BN / 2);
-  if ((e = run_gemm<T, FWD_GU>(a, round8(mtb * a.n_tiles), s, "gemm_fwd_gate_up")) != hipSuccess) return e;
-  a.n_tiles = d.d_model / T_BN;
-  if ((e = run_gemm<T, FWD_DOWN>(a, round8(mtb * a.n_tiles), s, "gemm_fwd_down")) != hipSuccess) return e;
-  return hipGetLastError();
+  a.mt_prefix = pre64;
+  const long t_gu = ragged_tiles(d, a, 2 * d.d_ff);
+  if (hipError_t e = run_f32<FWD_GU, FWD_GU>(a, t_gu, a, 0, s, "gemm_fwd_gate_up"); e != hipSuccess) return e;
+  const long t_dn = ragged_tiles(d, a, d.d_model);
+  return run_f32<FWD_DOWN, FWD_DOWN>(a, t_dn, a, 0, s, "gemm_fwd_down");
 }
 
 hipError_t ffn_bwd_f32(const moe_desc& d, const void* x, const void* xp, const void* dy, const void* dyp,
                        const int32_t* offsets, const void* wg, const void* wu, const void* wd, const void* saved,
-                       void* dxp, void* dwg, void* dwu, void* dwd, void* dgu, int32_t* pre, hipStream_t s) {
-  using T = float;
-  const size_t R = (size_t)rows_total(d), es = sizeof(T);
-  GemmArgs a = base_args(d, offsets, pre);
+                       void* dxp, void* dwg, void* dwu, void* dwd, void* dgu, const int32_t* pre64,
+                       const int32_t* order, hipStream_t s) {
+  const size_t R = (size_t)rows_total(d), es = sizeof(float);
+  GemmArgs a = base_args(d, offsets);
   a.x = x; a.xp = xp; a.dy = dy; a.dyp = dyp; a.wg = wg; a.wu = wu; a.wd = wd;
   a.gu = (void*)saved;
   a.h = (char*)saved + align256(R * 2 * d.d_ff * es);
   a.dgu = dgu;
-  const long mtb = mtile_bound(d);
-  const int G = d.local_count + d.n_shared;
-  hipError_t e;
-  a.n_tiles = d.d_ff / T_BN;
-  if ((e = run_gemm<T, BWD_DH>(a, round8(mtb * a.n_tiles), s, "gemm_bwd_dh")) != hipSuccess) return e;
-  a.out = dwd;
-  a.m_tiles = d.d_model / T_BM;
-  a.n_tiles = d.d_ff / T_BN;
-  if ((e = run_gemm<T, WG_DOWN>(a, round8((long)G * a.m_tiles * a.n_tiles), s, "gemm_wgrad_down")) != hipSuccess)
+  a.mt_prefix = pre64;
+  GemmArgs dh = a, dwn = a, dx = a, wgu = a;
+  dwn.out = dwd;
+  dwn.order = wgu.order = order;
+  wgu.out = dwg;
+  wgu.out2 = dwu;
+  dx.out = dxp;
+  const long t_dh = ragged_tiles(d, dh, d.d_ff), t_wd = wgrad_tiles(d, dwn, d.d_model, d.d_ff);
+  const long t_dx = ragged_tiles(d, dx, d.d_model), t_wgu = wgrad_tiles(d, wgu, 2 * d.d_ff, d.d_model);
+  // the weight gradients first, heaviest groups first: their K loops (a group's rows) vary, the others' do not
+  if (hipError_t e = run_f32<WG_DOWN, BWD_DH>(dwn, t_wd, dh, t_dh, s, "gemm_bwd_dh+wgrad_down"); e != hipSuccess)
     return e;
-  a.out = dwg;
-  a.out2 = dwu;
-  a.m_tiles = 2 * d.d_ff / T_BM;
-  a.n_tiles = d.d_model / T_BN;
-  if ((e = run_gemm<T, WG_GU>(a, round8((long)G * a.m_tiles * a.n_tiles), s, "gemm_wgrad_gate_up")) != hipSuccess)
-    return e;
-  a.out = dxp;
-  a.n_tiles = d.d_model / T_BN;
-  if ((e = run_gemm<T, BWD_DX>(a, round8(mtb * a.n_tiles), s, "gemm_bwd_dx")) != hipSuccess) return e;
-  return hipGetLastError();
+  return run_f32<WG_GU, BWD_DX>(wgu, t_wgu, dx, t_dx, s, "gemm_bwd_dx+wgrad_gate_up");
 }
 
 }  // namespace pcmoe
