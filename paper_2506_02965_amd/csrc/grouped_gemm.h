@@ -257,17 +257,80 @@ __device__ __forceinline__ bool decode_with(const GemmArgs& p, int bid, const De
   return true;
 }
 
-// Tile plan of the row-ragged contractions (one workgroup of 512 threads: at most 511 groups): pre0, pre1 and
-// pre2 = m-tile prefixes for bm0-, bm1- and bm2-row tiles; for bm1-row tiles also body1 = prefix of the m-tiles
-// other than the tails and tail1 = prefix of the tails (a last m-tile holding at most bm1 / 2 rows); order =
-// groups by decreasing row count (ties by index), and order[G] = 1 when all groups' row counts lie within 25% of
-// the largest (0 otherwise). It also sets zero[0 .. nzero) to 0 (the tile counters of the launches that follow).
-__global__ __launch_bounds__(512) void mtile_prefix_kernel(const int32_t* __restrict__ offsets, int Eloc, int S,
-                                                           int Tn, int bm0, int bm1, int bm2,
-                                                           int32_t* __restrict__ pre0, int32_t* __restrict__ pre1,
-                                                           int32_t* __restrict__ body1, int32_t* __restrict__ tail1,
-                                                           int32_t* __restrict__ pre2, int32_t* __restrict__ order,
-                                                           int32_t* __restrict__ zero, int nzero);
+// Tile plan of the row-ragged contractions (at most 511 groups): pre0, pre1 and pre2 = m-tile prefixes for bm0-,
+// bm1- and bm2-row tiles; for bm1-row tiles also body1 = prefix of the m-tiles other than the tails and tail1 =
+// prefix of the tails (a last m-tile holding at most bm1 / 2 rows); order = groups by decreasing row count (ties by
+// index), and order[G] = 1 when all groups' row counts lie within 25% of the largest (0 otherwise). zero[0 .. nzero)
+// is set to 0 (the tile counters of the launches that follow).
+struct PlanArgs {
+  const int32_t* offsets;
+  int Eloc, S, T, bm0, bm1, bm2;
+  int32_t *pre0, *pre1, *body1, *tail1, *pre2, *order, *zero;
+  int nzero;
+};
+// The plan, by one workgroup of NT threads; rows_s: 512 ints of LDS. A wavefront scans each prefix array 64 groups at
+// a time, so the plan costs one load of the offsets and two barriers.
+template <int NT>
+__device__ __forceinline__ void plan_block(const PlanArgs& a, int* rows_s) {
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = a.Eloc + a.S;
+  if (a.zero && tid < a.nzero) a.zero[tid] = 0;
+  for (int g = tid; g < 512; g += NT)
+    rows_s[g] = g < a.Eloc ? a.offsets[g + 1] - a.offsets[g] : g < G ? a.T : 0;
+  __syncthreads();
+  for (int g = tid; g < G; g += NT) {
+    const int rows = rows_s[g];
+    int rank = 0;
+    for (int h = 0; h < G; ++h) rank += (rows_s[h] > rows) || (rows_s[h] == rows && h < g);
+    a.order[rank] = g;
+  }
+  for (int which = w; which < 6; which += NT / 64) {
+    int carry = 0, lo = 0x7fffffff, hi = 0;
+    int32_t* out = which == 0 ? a.pre0 : which == 1 ? a.pre1 : which == 2 ? a.body1 : which == 3 ? a.tail1 : a.pre2;
+    if (which < 5 && lane == 0) out[0] = 0;
+    for (int g0 = 0; g0 < G; g0 += 64) {
+      const int g = g0 + lane, rows = rows_s[g];
+      if (which == 5) {
+        if (g < G) {
+          lo = min(lo, rows);
+          hi = max(hi, rows);
+        }
+        continue;
+      }
+      const int rem = rows % a.bm1, is_tail = (rem > 0 && 2 * rem <= a.bm1) ? 1 : 0;
+      const int bm = which == 0 ? a.bm0 : which == 4 ? a.bm2 : a.bm1;
+      int v = which == 3 ? is_tail : (rows + bm - 1) / bm - (which == 2 ? is_tail : 0);
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+      }
+      v += carry;
+      carry = __builtin_amdgcn_readlane(v, 63);
+      if (g < G) out[g + 1] = v;
+    }
+    if (which == 5) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, __shfl_xor(lo, o, 64));
+        hi = max(hi, __shfl_xor(hi, o, 64));
+      }
+      if (lane == 0) a.order[G] = (G > 0 && 4 * hi <= 5 * lo) ? 1 : 0;
+    }
+  }
+}
+__global__ __launch_bounds__(512) void tile_plan_kernel(PlanArgs a);
+
+// Few rows per expert (bf16): the forward's contractions with the weights streamed straight into registers. mt = 0: the
+// LDS tiles are the better choice (their grid has tile_grid workgroups).
+struct StreamPick {
+  int mt;  // 16-row blocks per workgroup
+  int nf;  // FWD_DOWN: 16-column blocks per wavefront
+};
+StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid);
+hipError_t stream_gate_up(const moe_desc& d, const StreamPick& k, const GemmArgs& a, const PlanArgs& plan,
+                          hipStream_t s, const char* name);
+hipError_t stream_down(const moe_desc& d, const StreamPick& k, const GemmArgs& a, hipStream_t s, const char* name);
 
 // fp32 path; pre64: m-tile prefix for 64-row tiles, order: groups by decreasing row count
 hipError_t ffn_fwd_f32(const moe_desc& d, const void* x, const void* xp, const int32_t* offsets, const void* wg,

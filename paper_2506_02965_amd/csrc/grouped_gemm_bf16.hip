@@ -1055,8 +1055,7 @@ static hipError_t run_shape(int shape, const GemmArgs& a, long tiles, hipStream_
 
 // Default shape per contraction; PCMOE_GEMM_TILES="<kind>=<shape>,..." overrides (kind 0..5 as in
 // GemmKind, shape as in kShapeName), e.g. "0=256x256s2,5=128x256s3".
-static long mtile_bound2(const moe_desc& d, int bm);
-static int tile_shape(int kind, const moe_desc& d) {
+static int forced_shape(int kind) {
   struct Overrides {  // parsed once (thread-safe static initialisation)
     int table[6] = {-1, -1, -1, -1, -1, -1};
     Overrides() {
@@ -1073,7 +1072,11 @@ static int tile_shape(int kind, const moe_desc& d) {
     }
   };
   static const Overrides ov;
-  if (ov.table[kind] >= 0) return ov.table[kind];
+  return ov.table[kind];
+}
+static long mtile_bound2(const moe_desc& d, int bm);
+static int tile_shape(int kind, const moe_desc& d) {
+  if (const int forced = forced_shape(kind); forced >= 0) return forced;
   // FWD_DOWN (N = d_model): when its 256x256 grid is one partial round of the chip, 192-row tiles still fit one
   // round and each costs about 3/4 of a 256-row tile. (The backward kinds run paired with a weight gradient,
   // which shares their shape.)
@@ -1140,15 +1143,10 @@ static Plan plan_at(const moe_desc& d, void* where) {
   pl.pre192 = (int32_t*)((char*)where + 5 * plan_part(d));
   return pl;
 }
-// (zero, nzero: counters the plan kernel also clears, for the launches that follow it)
-static Plan plan(const moe_desc& d, const int32_t* offsets, void* where, hipStream_t s, int32_t* zero = nullptr,
-                 int nzero = 0) {
-  Plan pl = plan_at(d, where);
-  KernelTimer kt("ffn_plan", s);
-  hipLaunchKernelGGL(mtile_prefix_kernel, dim3(1), dim3(512), 0, s, offsets, d.local_count, d.n_shared, d.T,
-                     d.dtype == MOE_BF16 ? 128 : 64, 256, 192, pl.pre128, pl.pre256, pl.body256, pl.tail256, pl.pre192,
-                     pl.order, zero, nzero);
-  return pl;
+// (zero, nzero: counters the plan also clears, for the launches that follow it)
+static PlanArgs plan_args(const moe_desc& d, const int32_t* offsets, const Plan& pl, int32_t* zero, int nzero) {
+  return PlanArgs{offsets, d.local_count, d.n_shared, d.T, d.dtype == MOE_BF16 ? 128 : 64, 256, 192, pl.pre128,
+                  pl.pre256, pl.body256, pl.tail256, pl.pre192, pl.order, zero, nzero};
 }
 
 static GemmArgs args_for(const moe_desc& d, const int32_t* offsets) {
@@ -1285,7 +1283,17 @@ hipError_t launch_ffn_fwd(const moe_desc& d, const void* x, const void* xp, cons
                           const void* wu, const void* wd, void* yp, void* saved, void*, hipStream_t s) {
   // the gate/up and down-projection tile counters (after the plan in the saved buffer), cleared by the plan kernel
   int* tickets = (int*)((char*)saved + saved_plan_offset(d) + align256(plan_bytes(d)));
-  Plan pl = plan(d, offsets, (char*)saved + saved_plan_offset(d), s, tickets, 2);
+  const Plan pl = plan_at(d, (char*)saved + saved_plan_offset(d));
+  const PlanArgs pa = plan_args(d, offsets, pl, tickets, 2);
+  StreamPick gu{0, 0}, down{0, 0};
+  if (d.dtype == MOE_BF16 && dynamic_tiles() != 2) {
+    if (forced_shape(FWD_GU) < 0) gu = stream_pick(d, FWD_GU, mtile_bound2(d, 256) * ((2 * d.d_ff + 255) / 256));
+    if (forced_shape(FWD_DOWN) < 0) down = stream_pick(d, FWD_DOWN, mtile_bound2(d, 192) * ((d.d_model + 255) / 256));
+  }
+  if (!gu.mt) {  // a streamed gate/up launch writes the plan itself
+    KernelTimer kt("ffn_plan", s);
+    hipLaunchKernelGGL(tile_plan_kernel, dim3(1), dim3(512), 0, s, pa);
+  }
   if (d.dtype != MOE_BF16) return ffn_fwd_f32(d, x, xp, offsets, wg, wu, wd, yp, saved, pl.pre128, s);
   const size_t R = (size_t)rows_total(d);
   GemmArgs a = args_for(d, offsets);
@@ -1299,7 +1307,10 @@ hipError_t launch_ffn_fwd(const moe_desc& d, const void* x, const void* xp, cons
     a_gu.tickets = tickets;
     a_down.tickets = tickets + 1;
   }
-  if ((e = run<FWD_GU>(prep_ragged<FWD_GU>(d, a_gu, pl, 2 * d.d_ff), s)) != hipSuccess) return e;
+  e = gu.mt ? stream_gate_up(d, gu, a, pa, s, kKindName[FWD_GU])
+            : run<FWD_GU>(prep_ragged<FWD_GU>(d, a_gu, pl, 2 * d.d_ff), s);
+  if (e != hipSuccess) return e;
+  if (down.mt) return stream_down(d, down, a, s, kKindName[FWD_DOWN]);
   return run<FWD_DOWN>(prep_ragged<FWD_DOWN>(d, a_down, pl, d.d_model), s);
 }
 

@@ -275,60 +275,9 @@ __global__ __launch_bounds__(C::NT) void gemm_f32_kernel(GemmArgs pa, GemmArgs p
 
 // m-tile prefixes over groups for two tile heights: pre[g] = sum_{g' < g} ceil(rows_g' / bm); and
 // the groups ordered by decreasing row count (ties by index).
-__global__ __launch_bounds__(512) void mtile_prefix_kernel(const int32_t* __restrict__ offsets, int Eloc, int S,
-                                                           int Tn, int bm0, int bm1, int bm2,
-                                                           int32_t* __restrict__ pre0, int32_t* __restrict__ pre1,
-                                                           int32_t* __restrict__ body1, int32_t* __restrict__ tail1,
-                                                           int32_t* __restrict__ pre2, int32_t* __restrict__ order,
-                                                           int32_t* __restrict__ zero, int nzero) {
-  __shared__ int buf[5][2][512];
+__global__ __launch_bounds__(512) void tile_plan_kernel(PlanArgs a) {
   __shared__ int rows_s[512];
-  const int g = threadIdx.x;
-  if (zero && g < nzero) zero[g] = 0;
-  const int G = Eloc + S;
-  int rows = 0;
-  if (g < Eloc) rows = offsets[g + 1] - offsets[g];
-  else if (g < G) rows = Tn;
-  // bm1 tiles: a last m-tile with at most half its rows is a tail, counted apart
-  const int rem1 = rows % bm1, is_tail = (rem1 > 0 && 2 * rem1 <= bm1) ? 1 : 0;
-  buf[0][0][g] = (rows + bm0 - 1) / bm0;
-  buf[1][0][g] = (rows + bm1 - 1) / bm1;
-  buf[2][0][g] = (rows + bm1 - 1) / bm1 - is_tail;
-  buf[3][0][g] = is_tail;
-  buf[4][0][g] = (rows + bm2 - 1) / bm2;
-  rows_s[g] = rows;
-  __syncthreads();
-  if (g < G) {
-    int rank = 0;
-    for (int h = 0; h < G; ++h) rank += (rows_s[h] > rows) || (rows_s[h] == rows && h < g);
-    order[rank] = g;
-  }
-  if (g == 0) {  // order[G] = 1 when every group's row count is within 25% of the largest
-    int lo = rows_s[0], hi = rows_s[0];
-    for (int h = 1; h < G; ++h) {
-      lo = min(lo, rows_s[h]);
-      hi = max(hi, rows_s[h]);
-    }
-    order[G] = (G > 0 && 4 * hi <= 5 * lo) ? 1 : 0;
-  }
-  int cur = 0;
-  for (int off = 1; off < 512; off <<= 1) {
-#pragma unroll
-    for (int w = 0; w < 5; ++w) {
-      int x = buf[w][cur][g];
-      if (g >= off) x += buf[w][cur][g - off];
-      buf[w][cur ^ 1][g] = x;
-    }
-    cur ^= 1;
-    __syncthreads();
-  }
-  if (g <= G) {
-    pre0[g] = (g == 0) ? 0 : buf[0][cur][g - 1];
-    pre1[g] = (g == 0) ? 0 : buf[1][cur][g - 1];
-    body1[g] = (g == 0) ? 0 : buf[2][cur][g - 1];
-    tail1[g] = (g == 0) ? 0 : buf[3][cur][g - 1];
-    pre2[g] = (g == 0) ? 0 : buf[4][cur][g - 1];
-  }
+  plan_block<512>(a, rows_s);
 }
 
 // ------------------------------------------------------------------------- host side

@@ -1,0 +1,405 @@
+// Expert passes over few rows per expert (decode steps, short prompts, small micro-batches) in bf16.
+//
+// With few rows per expert a contraction is bound by reading the weights once. The LDS-tiled kernels
+// (grouped_gemm_bf16.hip) then run one workgroup per CU that waits for each K-tile's round trip. Here the weights
+// never pass through LDS: each wavefront reads 64 contiguous bytes of 16 weight rows per load straight into MFMA
+// operand registers, several loads ahead, and the small register and LDS footprint leaves two and more workgroups on a
+// CU. The weights are the MFMA's first operand, the activations' rows the second, so that a lane's four accumulators
+// are four consecutive output columns of one row.
+//   * stream_split_kernel (up to 8 rows per group): 64 output columns of 16 rows, the wavefronts split K and their
+//     partial sums meet in LDS once at the end, in wavefront order (deterministic);
+//   * stream_rows_kernel (up to about 100): the wavefronts split the columns and share 32, 64 or 128 rows through LDS.
+// The group, row chunk and columns of a workgroup come from the offsets alone (a scan over the wavefront), so no tile
+// plan has to be launched first; the plan that the backward reads is written by one extra workgroup of FWD_GU.
+// Measured (layer forward, us, LDS tiles before -> now; bound by the weights at 5.4-5.8 TB/s):
+//   T=24, d=4096, f=14336, E=8, top-2: gate/up 370 -> 334, down 301 -> 175;
+//   T=1, d=2048, f=1408, E=64, top-6, 2 shared: gate/up 29 -> 23, down 34 -> 12;
+//   T=777, d=1024, f=2816, E=16, top-2: gate/up 63 -> 58, down 62 -> 35.
+#include "grouped_gemm.h"
+
+#include <algorithm>
+
+namespace pcmoe {
+
+__device__ __forceinline__ Chunk buf_ld16(__amdgpu_buffer_rsrc_t r, int voff) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+  Chunk c;
+  c.w[0] = v.x;
+  c.w[1] = v.y;
+  c.w[2] = v.z;
+  c.w[3] = v.w;
+  return c;
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+constexpr int ST_COLS = 64;         // output columns (FWD_GU: 32 gate and 32 up columns) of a K-splitting workgroup
+constexpr int ST_KS = 4;            // its wavefronts
+constexpr int ST_OOR = 0x7fffff00;  // a byte offset past every operand's range: the load returns zeros
+
+// Workgroup -> (group, row chunk of `chunk` rows, column block). Lane l of a wavefront counts the chunks of the groups
+// [l NS, l NS + NS) (one batch of loads), a scan over the lanes finds the lane whose groups hold the tile, and its
+// groups are then walked. Consecutive tiles, the row chunks of one column block first, stay on one XCD, whose L2 then
+// serves the chunks' repeated weight reads.
+struct StreamTile {
+  int g, row0, rows, ch, nb;
+};
+template <int NS>
+__device__ __forceinline__ bool stream_decode_ns(const GemmArgs& p, int bid, int chunk, int n_blocks, StreamTile& t) {
+  const int G = p.Eloc + p.S, lane = threadIdx.x & 63, g0 = lane * NS;
+  int off[NS + 1], sum = 0;
+#pragma unroll
+  for (int s = 0; s <= NS; ++s) off[s] = p.offsets[min(g0 + s, p.Eloc)];
+  auto rows_of = [&](int g, int lo, int hi) { return g < p.Eloc ? hi - lo : g < G ? p.T : 0; };
+#pragma unroll
+  for (int s = 0; s < NS; ++s) sum += (rows_of(g0 + s, off[s], off[s + 1]) + chunk - 1) / chunk;
+  int incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += u;
+  }
+  const int total = __builtin_amdgcn_readlane(incl, 63) * n_blocks;
+  const int x = bid & 7, lb = bid >> 3, q = total >> 3, r = total & 7;
+  if (lb >= q + (x < r ? 1 : 0)) return false;
+  const int L = x * q + min(x, r) + lb;
+  const int j = __popcll(__ballot(incl * n_blocks <= L));  // the lane holding tile L (L < total: j < 64)
+  int l = L - __builtin_amdgcn_readlane(incl - sum, j) * n_blocks, nch = 1;
+  bool found = false;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int lo = __builtin_amdgcn_readlane(off[s], j), hi = __builtin_amdgcn_readlane(off[s + 1], j);
+    const int rows = rows_of(j * NS + s, lo, hi), n = (rows + chunk - 1) / chunk;
+    if (!found && l < n * n_blocks) {
+      found = true;
+      t.g = j * NS + s;
+      t.row0 = lo;
+      t.rows = rows;
+      nch = n;
+    }
+    if (!found) l -= n * n_blocks;
+  }
+  t.nb = __builtin_amdgcn_readfirstlane(l / nch);
+  t.ch = __builtin_amdgcn_readfirstlane(l - (l / nch) * nch);
+  return true;
+}
+__device__ __forceinline__ bool stream_decode(const GemmArgs& p, int bid, int chunk, int n_blocks, StreamTile& t) {
+  const int G = p.Eloc + p.S;
+  if (G <= 64) return stream_decode_ns<1>(p, bid, chunk, n_blocks, t);
+  if (G <= 128) return stream_decode_ns<2>(p, bid, chunk, n_blocks, t);
+  return stream_decode_ns<8>(p, bid, chunk, n_blocks, t);
+}
+
+__device__ __forceinline__ uint2 pack4(const floatx4& v) {
+  return uint2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
+// Four consecutive columns of one row: G, U and H = silu(G) U, or the down projection's output.
+__device__ __forceinline__ void store_gu(const GemmArgs& p, size_t row, int col, const floatx4& g, const floatx4& u) {
+  floatx4 h;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) h[e] = g[e] * __builtin_amdgcn_rcpf(1.f + __expf(-g[e])) * u[e];
+  bf16* gu = (bf16*)p.gu + row * 2 * p.f + col;
+  *reinterpret_cast<uint2*>(gu) = pack4(g);
+  *reinterpret_cast<uint2*>(gu + p.f) = pack4(u);
+  *reinterpret_cast<uint2*>((bf16*)p.h + row * p.f + col) = pack4(h);
+}
+__device__ __forceinline__ void store_out(const GemmArgs& p, size_t row, int col, const floatx4& v) {
+  *reinterpret_cast<uint2*>((bf16*)p.out + row * p.d + col) = pack4(v);
+}
+
+// Up to 16 rows of a group: the wavefronts split K. KIND FWD_GU or FWD_DOWN.
+template <int KIND>
+__global__ __launch_bounds__(64 * ST_KS) void stream_split_kernel(GemmArgs p, PlanArgs plan, int n_blocks, int tiles) {
+  constexpr int NF = ST_COLS / 16, KS = ST_KS;
+  constexpr int PITCH = ST_COLS + 4;
+  __shared__ __align__(16) float red[KS * 16 * PITCH];
+  static_assert(sizeof(red) >= 512 * sizeof(int), "the plan keeps its row counts here");
+  if (KIND == FWD_GU && (int)blockIdx.x >= tiles) {
+    plan_block<64 * KS>(plan, (int*)red);
+    return;
+  }
+  StreamTile t;
+  if (!stream_decode(p, blockIdx.x, 16, n_blocks, t)) return;
+  const int lane = threadIdx.x & 63, q = lane >> 4, li = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int K = KIND == FWD_GU ? p.d : p.f;
+  const bool routed = t.g < p.Eloc;
+  // rows of the activations: x_perm / H rows of a routed group, x / H rows of a shared expert
+  const size_t rs = routed ? (size_t)t.row0 : (size_t)p.rows_cap + (size_t)(t.g - p.Eloc) * p.T;
+  const char* xb = KIND == FWD_GU ? (routed ? (const char*)p.xp + (size_t)t.row0 * K * 2 : (const char*)p.x)
+                                  : (const char*)p.h + rs * K * 2;
+  const int m0 = t.ch * 16, m_rows = min(t.rows - m0, 16);
+  const auto xr = buf_rsrc(xb + (size_t)m0 * K * 2, (size_t)m_rows * K * 2);
+  // weight rows of the column block: FWD_GU 32 gate rows and the same 32 up rows, FWD_DOWN 64 rows of W_down
+  const size_t wsz = (size_t)p.d * p.f * 2;
+  const int wrow = t.nb * (KIND == FWD_GU ? ST_COLS / 2 : ST_COLS);
+  const char* w0 = (const char*)(KIND == FWD_GU ? p.wg : p.wd) + t.g * wsz + (size_t)wrow * K * 2;
+  const char* w1 = KIND == FWD_GU ? (const char*)p.wu + t.g * wsz + (size_t)wrow * K * 2 : w0;
+  constexpr int F0 = KIND == FWD_GU ? NF / 2 : NF;  // weight blocks read through the first resource
+  const auto wr0 = buf_rsrc(w0, (size_t)16 * F0 * K * 2);
+  const auto wr1 = buf_rsrc(w1, (size_t)16 * F0 * K * 2);
+
+  const int units = K / 64, rounds = (units + KS - 1) / KS;
+  const int lane_off = li * K * 2 + q * 16;
+  floatx4 acc[NF];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  Chunk wb[2][NF][2], xv[2][2];
+  // step r of this wavefront: bytes [128 u, 128 u + 128) of each row, u = r KS + w (zeros past the last unit)
+  auto load = [&](int r, Chunk(&wbuf)[NF][2], Chunk(&xbuf)[2]) {
+    const int u = r * KS + w;
+    const int vo = u < units ? lane_off + u * 128 : ST_OOR;
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      const int o = vo + (i % F0) * 16 * K * 2 * (u < units ? 1 : 0);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) wbuf[i][h] = buf_ld16(i < F0 ? wr0 : wr1, o + 64 * h);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) xbuf[h] = buf_ld16(xr, vo + 64 * h);
+  };
+  auto mul = [&](const Chunk(&wbuf)[NF][2], const Chunk(&xbuf)[2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < NF; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wbuf[i][h]),
+                                                         __builtin_bit_cast(bf16x8, xbuf[h]), acc[i], 0, 0, 0);
+  };
+  // the scheduling barriers keep each step's loads behind the MFMAs before them: left alone, the compiler gathers both
+  // steps' loads at the loop's end and waits for all of them at its top
+  load(0, wb[0], xv[0]);
+  __builtin_amdgcn_sched_barrier(0);
+  load(1, wb[1], xv[1]);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int r = 0; r < rounds; r += 2) {
+    mul(wb[0], xv[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    load(r + 2, wb[0], xv[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(wb[1], xv[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    load(r + 3, wb[1], xv[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // Sum over the wavefronts in their order and write out: thread -> (row, 4 columns).
+#pragma unroll
+  for (int i = 0; i < NF; ++i) *reinterpret_cast<floatx4*>(&red[(w * 16 + li) * PITCH + 16 * i + 4 * q]) = acc[i];
+  __syncthreads();
+  constexpr int QC = (KIND == FWD_GU ? ST_COLS / 2 : ST_COLS) / 4;  // column quads of the outputs
+  const int rr = threadIdx.x / QC, c = (threadIdx.x % QC) * 4;
+  if (rr >= m_rows) return;
+  floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f}, u = v;
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+    const float* src = &red[(k * 16 + rr) * PITCH + c];
+    v += *reinterpret_cast<const floatx4*>(src);
+    if (KIND == FWD_GU) u += *reinterpret_cast<const floatx4*>(src + ST_COLS / 2);
+  }
+  const size_t row = rs + m0 + rr;
+  if (KIND == FWD_GU) store_gu(p, row, wrow + c, v, u);
+  else store_out(p, row, wrow + c, v);
+}
+
+// Up to 16 MT rows of a group: the wavefronts share the rows and split the columns.
+//   * each of the 4 wavefronts owns 16 NF weight rows (FWD_GU: 16 gate rows and the same 16 up rows) over the whole K
+//     and keeps D steps of 64 k of them in flight in registers;
+//   * the group's rows (up to 16 MT) pass through LDS, 64 k at a time in two stages, filled from registers loaded two
+//     steps ahead: one barrier per step, and no load is waited for in the step that issues it;
+//   * the accumulators hold four consecutive output columns of one row per lane, so SwiGLU and the stores need no LDS.
+// X stage: 128-byte rows, 16-byte chunk c of row r at c ^ swz(r).
+__device__ __forceinline__ int xs_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+
+template <int KIND, int MT, int NF, int D>
+__global__ __launch_bounds__(256, 2) void stream_rows_kernel(GemmArgs p, PlanArgs plan, int n_blocks, int tiles) {
+  static_assert(D % 2 == 0 && (KIND != FWD_GU || NF == 2), "");
+  constexpr int ROWS = 16 * MT, XL = ROWS * 8 / 256 > 0 ? ROWS * 8 / 256 : 1;  // 16-byte chunks of X per thread and step
+  constexpr int COLS = KIND == FWD_GU ? 64 : 64 * NF;                           // output columns of the workgroup
+  __shared__ __align__(16) char xs[2][ROWS * 128 > 2048 ? ROWS * 128 : 2048];
+  if (KIND == FWD_GU && (int)blockIdx.x >= tiles) {
+    plan_block<256>(plan, (int*)xs);
+    return;
+  }
+  StreamTile t;
+  if (!stream_decode(p, blockIdx.x, ROWS, n_blocks, t)) return;
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, li = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int K = KIND == FWD_GU ? p.d : p.f, KB = K * 2, units = K / 64;
+  const bool routed = t.g < p.Eloc;
+  const size_t rs = routed ? (size_t)t.row0 : (size_t)p.rows_cap + (size_t)(t.g - p.Eloc) * p.T;
+  const char* xb = KIND == FWD_GU ? (routed ? (const char*)p.xp + (size_t)t.row0 * KB : (const char*)p.x)
+                                  : (const char*)p.h + rs * KB;
+  const int m0 = t.ch * ROWS, m_rows = min(t.rows - m0, ROWS);
+  const auto xr = buf_rsrc(xb + (size_t)m0 * KB, (size_t)m_rows * KB);
+  const size_t wsz = (size_t)p.d * p.f * 2;
+  const int wrow = t.nb * COLS + w * (KIND == FWD_GU ? 16 : 16 * NF);  // the wavefront's first output column
+  const char* w0 = (const char*)(KIND == FWD_GU ? p.wg : p.wd) + t.g * wsz + (size_t)wrow * KB;
+  const char* w1 = KIND == FWD_GU ? (const char*)p.wu + t.g * wsz + (size_t)wrow * KB : w0;
+  constexpr int F0 = KIND == FWD_GU ? 1 : NF;
+  const auto wr0 = buf_rsrc(w0, (size_t)16 * F0 * KB);
+  const auto wr1 = buf_rsrc(w1, (size_t)16 * F0 * KB);
+
+  Chunk wb[D][NF][2], xv[D][XL];
+  auto load_w = [&](int u, Chunk(&buf)[NF][2]) {
+    const int vo = li * KB + q * 16 + u * 128;
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        buf[i][h] = buf_ld16(i < F0 ? wr0 : wr1, u < units ? vo + (i % F0) * 16 * KB + 64 * h : ST_OOR);
+  };
+  auto load_x = [&](int u, Chunk(&buf)[XL]) {
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+      const int c = tid + 256 * i;  // rows past the chunk's last one lie past the buffer: zeros
+      buf[i] = buf_ld16(xr, u < units ? (c >> 3) * KB + (c & 7) * 16 + u * 128 : ST_OOR);
+    }
+  };
+  auto put_x = [&](int stage, const Chunk(&buf)[XL]) {
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+      const int c = tid + 256 * i, r = c >> 3;
+      if (ROWS * 8 >= 256 || r < ROWS) st_chunk(xs[stage] + r * 128 + (((c & 7) ^ xs_swz(r)) << 4), buf[i]);
+    }
+  };
+  floatx4 acc[MT][NF];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < NF; ++i) acc[m][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int swz = xs_swz(li);  // every 16-row block repeats it
+  auto mul = [&](int stage, const Chunk(&buf)[NF][2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const Chunk x = ld_chunk(xs[stage] + (16 * m + li) * 128 + (((4 * h + q) ^ swz) << 4));
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+          acc[m][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, buf[i][h]),
+                                                              __builtin_bit_cast(bf16x8, x), acc[m][i], 0, 0, 0);
+      }
+  };
+  // Loads complete in order: a step's rows are issued ahead of its weights and as early, so that waiting for them never
+  // means waiting for weights of a later step.
+#pragma unroll
+  for (int s = 0; s < D - 1; ++s) {
+    load_x(s, xv[s]);
+    load_w(s, wb[s]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  put_x(0, xv[0]);
+  for (int u0 = 0; u0 < units; u0 += D) {
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      const int u = u0 + s;
+      if (u >= units) break;
+      // stage u is filled, and every wavefront has left step u - 1, whose stage this step refills
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      load_x(u + D - 1, xv[(s + D - 1) % D]);
+      load_w(u + D - 1, wb[(s + D - 1) % D]);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(s & 1, wb[s]);
+      __builtin_amdgcn_sched_barrier(0);
+      put_x((s + 1) & 1, xv[(s + 1) % D]);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int r = 16 * m + li;
+    if (r >= m_rows) continue;
+    const size_t row = rs + m0 + r;
+    if (KIND == FWD_GU) {
+      store_gu(p, row, wrow + 4 * q, acc[m][0], acc[m][NF - 1]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NF; ++i) store_out(p, row, wrow + 16 * i + 4 * q, acc[m][i]);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------- host side
+
+// Upper bound on the row chunks: each routed chunk holds at least one row, and all but one per group are full.
+static long chunk_bound(const moe_desc& d, int chunk) {
+  const long slots = (long)d.T * d.top_k;
+  const long routed = std::min(slots, (slots + (long)d.local_count * (chunk - 1)) / chunk);
+  return routed + (long)d.n_shared * ((d.T + chunk - 1) / chunk);
+}
+
+static unsigned grid_of(long wgs) { return (unsigned)((wgs + 7) / 8 * 8); }
+
+template <int KIND>
+static hipError_t run_split(const moe_desc& d, const GemmArgs& a, const PlanArgs& plan, hipStream_t s,
+                            const char* name) {
+  const int n_blocks = KIND == FWD_GU ? d.d_ff / (ST_COLS / 2) : d.d_model / ST_COLS;
+  const unsigned tiles = grid_of(chunk_bound(d, 16) * n_blocks);
+  KernelTimer kt(name, s);
+  hipLaunchKernelGGL((stream_split_kernel<KIND>), dim3(tiles + (KIND == FWD_GU ? 1 : 0)), dim3(64 * ST_KS), 0, s, a,
+                     plan, n_blocks, (int)tiles);
+  return hipGetLastError();
+}
+template <int KIND, int MT, int NF, int D>
+static hipError_t run_rows(const moe_desc& d, const GemmArgs& a, const PlanArgs& plan, hipStream_t s,
+                           const char* name) {
+  const int n_blocks = KIND == FWD_GU ? d.d_ff / 64 : d.d_model / (64 * NF);
+  const unsigned tiles = grid_of(chunk_bound(d, 16 * MT) * n_blocks);
+  KernelTimer kt(name, s);
+  hipLaunchKernelGGL((stream_rows_kernel<KIND, MT, NF, D>), dim3(tiles + (KIND == FWD_GU ? 1 : 0)), dim3(256), 0, s,
+                     a, plan, n_blocks, (int)tiles);
+  return hipGetLastError();
+}
+
+// Which streaming kernel a contraction takes, by the expected rows per group (every expert equally likely) and the
+// workgroups its grid has. Each line was drawn from timings of all the variants and of the LDS tiles over eight layer
+// shapes (d 256 to 4096, f 512 to 14336, 4 to 128 experts, with and without shared experts, uniform and Zipf-skewed)
+// at 1 to 256 rows per group:
+//   * up to 8 rows, at most 5 workgroups per CU: the split over K (2-20% under the 32-row kernel, which is 5-20%
+//     under it beyond 5 per CU);
+//   * up to 24, 50 and 100 rows: 32-, 64- and 128-row chunks (the next size up costs 5-30% more below each line, the
+//     previous one 5-50% above it);
+//   * past 100 rows the LDS tiles take over (at 128 rows they are 0-25% faster, at 64 rows 0-60% slower), except
+//     where their grid would leave half the CUs or more idle: the chunks are 10-60% faster there up to 200 rows.
+// FWD_DOWN at 33 rows and more takes 128 columns per workgroup as long as that leaves one workgroup per CU (at 64 rows
+// 16% faster with d = 4096, 14% slower with d = 1024 and 16 experts).
+StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid) {
+  StreamPick none{0, 0}, split{1, 1};
+  if (d.dtype != MOE_BF16) return none;
+  const int G = d.local_count + d.n_shared;
+  const double rows = ((double)d.T * d.top_k * d.local_count / d.n_experts + (double)d.T * d.n_shared) / G;
+  const int cols = kind == FWD_GU ? d.d_ff : d.d_model, cus = device_cus();
+  const long split_wgs = chunk_bound(d, 16) * (cols / (kind == FWD_GU ? ST_COLS / 2 : ST_COLS));
+  if (rows <= 8 && split_wgs <= 5L * cus) return split;
+  if (rows > (tile_grid <= cus / 2 ? 200 : 100)) return none;
+  const int mt = rows <= 24 ? 2 : rows <= 50 ? 4 : 8;
+  const bool wide = kind == FWD_DOWN && mt > 2 && chunk_bound(d, 16 * mt) * (cols / 128) >= cus;
+  return StreamPick{mt, wide ? 2 : 1};
+}
+
+hipError_t stream_gate_up(const moe_desc& d, const StreamPick& k, const GemmArgs& a, const PlanArgs& plan,
+                          hipStream_t s, const char* name) {
+  switch (k.mt) {
+    case 1: return run_split<FWD_GU>(d, a, plan, s, name);
+    case 2: return run_rows<FWD_GU, 2, 2, 4>(d, a, plan, s, name);
+    case 4: return run_rows<FWD_GU, 4, 2, 4>(d, a, plan, s, name);
+    default: return run_rows<FWD_GU, 8, 2, 2>(d, a, plan, s, name);
+  }
+}
+hipError_t stream_down(const moe_desc& d, const StreamPick& k, const GemmArgs& a, hipStream_t s, const char* name) {
+  const PlanArgs none{};
+  switch (k.mt) {
+    case 1: return run_split<FWD_DOWN>(d, a, none, s, name);
+    case 2: return run_rows<FWD_DOWN, 2, 1, 4>(d, a, none, s, name);
+    case 4:
+      return k.nf == 2 ? run_rows<FWD_DOWN, 4, 2, 4>(d, a, none, s, name)
+                       : run_rows<FWD_DOWN, 4, 1, 4>(d, a, none, s, name);
+    default:
+      return k.nf == 2 ? run_rows<FWD_DOWN, 8, 2, 4>(d, a, none, s, name)
+                       : run_rows<FWD_DOWN, 8, 1, 4>(d, a, none, s, name);
+  }
+}
+
+}  // namespace pcmoe

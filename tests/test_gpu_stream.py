@@ -1,0 +1,72 @@
+"""The bf16 expert GEMMs of few rows per expert (weights streamed into registers) where their row chunks (16, 32, 64 and
+128 rows), column blocks and 64-deep K steps end, and the scan that finds a workgroup's group among up to 64, 128 and
+more groups. The backward reads the tile plan that the gate/up launch wrote."""
+import numpy as np
+import pytest
+
+from paper_2506_02965_amd.synth import LayerConfig, make_inputs
+from gpu_util import check_full, log, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _fill(E, edges, total):
+    """Rows per expert: the edges, zeros between, and the rest spread over the remaining experts."""
+    left = E - len(edges)
+    rest = total - sum(edges)
+    assert rest >= 0
+    return list(edges) + [rest // left + (1 if i < rest % left else 0) for i in range(left)]
+
+
+def _case(T, d, f, E, edges, seed, **kw):
+    cfg = LayerConfig("st", T=T, d=d, f=f, E=E, k=2, bias="party", parties=T, seed=seed, **kw)
+    return cfg, _fill(E, edges, 2 * T)
+
+
+CASES = {
+    # expected rows per group <= 8: the K-splitting kernel (16-row chunks)
+    "split": _case(48, 256, 384, 16, [0, 1, 15, 16, 17, 33, 0], 71),
+    "split_k_remainder_shared": _case(24, 128, 128, 12, [16, 0, 17], 72, n_shared=2),
+    "split_66_groups": _case(130, 128, 256, 64, [0, 16, 1, 40], 73, n_shared=2),
+    # <= 24: 32-row chunks
+    "rows32": _case(130, 256, 384, 16, [0, 1, 31, 32, 33, 65], 74),
+    "rows32_130_groups": _case(700, 128, 128, 130, [0, 32, 33], 75),
+    # <= 50: 64-row chunks, one and two column blocks per wavefront of the down projection
+    "rows64": _case(300, 256, 640, 16, [0, 63, 64, 65, 129, 1], 76, n_shared=1),
+    "rows64_wide": _case(640, 1024, 128, 40, [0, 63, 64, 65, 130], 77),
+    # <= 100 (and up to 200 where the tile grid is small): 128-row chunks
+    "rows128": _case(515, 384, 256, 8, [0, 127, 128, 129, 257, 1], 78),
+    "rows128_wide": _case(1100, 1024, 128, 40, [0, 127, 128, 129, 258], 79),
+}
+
+
+def forced(inp, counts):
+    T = inp.cfg.T
+    assert sum(counts) == 2 * T and max(counts) <= T
+    slots = np.repeat(np.arange(len(counts)), counts)  # a token's two slots lie T apart: different experts
+    inp.logit_bias[:] = -1e4
+    t = np.arange(T)
+    inp.logit_bias[t, slots[:T]] = 2e4
+    inp.logit_bias[t, slots[T:]] = 1e4
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_stream_edges(name):
+    cfg, counts = CASES[name]
+    log(f"[stream] {name}")
+    inp = make_inputs(cfg, with_dy=True)
+    forced(inp, counts)
+    layer, _ = run_gpu(cfg, inp)
+    assert np.array_equal(layer.counts.cpu().numpy(), counts)
+    errs = check_full(cfg, inp, layer)
+    log(f"[stream] {name}: " + " ".join(f"{k}={v:.2e}" for k, v in errs.items()))
+
+
+def test_stream_shard_one_token():
+    """A shard that hosts a quarter of the experts, and a single token (most groups empty)."""
+    for cfg in (LayerConfig("st1", T=130, d=256, f=128, E=32, k=4, local_begin=8, local_count=8, n_shared=1,
+                            router_backward=False, seed=81),
+                LayerConfig("st2", T=1, d=256, f=384, E=64, k=6, n_shared=2, seed=82)):
+        inp = make_inputs(cfg, with_dy=True)
+        layer, _ = run_gpu(cfg, inp)
+        check_full(cfg, inp, layer)
