@@ -77,6 +77,22 @@ __device__ __forceinline__ void st_chunk_nt(void* p, const Chunk& c) {
   const u32x4 v = {c.w[0], c.w[1], c.w[2], c.w[3]};
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
+// 16 bytes from a buffer of `bytes` bytes (below 2^31 - 256, p wave-uniform) at byte offset voff: zeros at and past the
+// end, so kBufPast skips a load without a branch.
+constexpr int kBufPast = 0x7fffff00;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ Chunk buf_ld16(__amdgpu_buffer_rsrc_t r, int voff) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+  Chunk c;
+  c.w[0] = v.x;
+  c.w[1] = v.y;
+  c.w[2] = v.z;
+  c.w[3] = v.w;
+  return c;
+}
 __device__ __forceinline__ Chunk zero_chunk() {
   Chunk c;
   c.w[0] = c.w[1] = c.w[2] = c.w[3] = 0u;

@@ -327,37 +327,39 @@ __global__ __launch_bounds__(256) void route_dlogits_kernel(int Tn, int E, int k
         if (e < E) dl[(size_t)t * E + e] = val;
       }
     } else {
-      // p over all E experts; g = dgate scattered onto E
-      float M = -INFINITY;
-      for (int e = lane; e < E; e += 64) M = fmaxf(M, logits[(size_t)t * E + e]);
+      // p over all E experts (up to 4 per lane); g = dgate scattered onto E
+      constexpr int NQ = 4;  // E <= 256
+      float p[NQ], g[NQ], M = -INFINITY, zp = 0.f, spg = 0.f;
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        const int e = lane + 64 * n;
+        p[n] = e < E ? logits[(size_t)t * E + e] : -INFINITY;
+        M = fmaxf(M, p[n]);
+      }
       M = wave_max(M);
-      float zp = 0.f;
-      for (int e = lane; e < E; e += 64) zp += expf(logits[(size_t)t * E + e] - M);
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        p[n] = lane + 64 * n < E ? expf(p[n] - M) : 0.f;
+        zp += p[n];
+        g[n] = 0.f;
+      }
       const float Z = wave_sum(zp);
-      float spg = 0.f;
-      for (int e0 = 0; e0 < E; e0 += 64) {
-        int e = e0 + lane;
-        float g = 0.f;
-        for (int jj = 0; jj < k; ++jj) {
-          int i2 = __shfl(ij, jj, 64);
-          float g2 = __shfl(gj, jj, 64);
-          if (e == i2) g = g2;
-        }
-        float p = (e < E) ? expf(logits[(size_t)t * E + e] - M) / Z : 0.f;
-        spg += p * g;
+      for (int jj = 0; jj < k; ++jj) {
+        const int i2 = __builtin_amdgcn_readlane(ij, jj);
+        const float g2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(gj), jj));
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+          if (lane + 64 * n == i2) g[n] = g2;
+      }
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        p[n] = p[n] / Z;
+        spg += p[n] * g[n];
       }
       const float S = wave_sum(spg);
-      for (int e0 = 0; e0 < E; e0 += 64) {
-        int e = e0 + lane;
-        float p = 0.f, g = 0.f;
-        if (e < E) p = expf(logits[(size_t)t * E + e] - M) / Z;
-        for (int jj = 0; jj < k; ++jj) {
-          int i2 = __shfl(ij, jj, 64);
-          float g2 = __shfl(gj, jj, 64);
-          if (e == i2) g = g2;
-        }
-        if (e < E) dl[(size_t)t * E + e] = p * (g - S);
-      }
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+        if (lane + 64 * n < E) dl[(size_t)t * E + lane + 64 * n] = p[n] * (g[n] - S);
     }
   }
 }
@@ -373,9 +375,8 @@ struct alignas(JJ * sizeof(T) < 16 ? JJ * sizeof(T) : 16) XRow {  // tensors are
 };
 
 // JJ columns per lane: 4 for up to 16 experts (narrower workgroups, so that 256 of them need only 64 token
-// chunks of partial sums: measured 9 us against 12 us for 8 columns and 128 chunks at T=4096, d=1024), 8 while the
-// accumulators (JJ x NET tiles) fit, fewer for many experts.
-constexpr int dw_cols_per_lane(int net) { return net == 1 ? 4 : net <= 2 ? 8 : 16 / net > 0 ? 16 / net : 1; }
+// chunks of partial sums: measured 9 us against 12 us for 8 columns and 128 chunks at T=4096, d=1024), 8 up to 32.
+constexpr int dw_cols_per_lane(int net) { return net == 1 ? 4 : 8; }
 
 template <typename T, int NET, int JJ>
 __global__ __launch_bounds__(256) void route_dw_partial_kernel(int Tn, int d, int E, int tok_per_chunk,
@@ -432,6 +433,92 @@ __global__ __launch_bounds__(256) void route_dw_partial_kernel(int Tn, int d, in
     }
 }
 
+// The same partial sums for more than 32 experts. A wavefront holds 64 experts x 16 chunks of columns and steps through
+// its tokens 4 at a time with one 16-byte load of dl (lane (q, i): token t + q, experts 4 i .. 4 i + 3, one per MFMA
+// row) and one of x (its chunk of token t + q) per 4 N MFMAs (N columns in a chunk), 16 tokens ahead of the MFMAs.
+// Bound by the fp32 MFMAs. T = 8192, d = 2048, E = 256: 85 us (56 us of MFMA at the peak rate), 184 with one column and
+// one 4-byte load of dl per MFMA; T = 16384, E = 64: 47 us, 81 before.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256, 2) void route_dw_wide_kernel(int Tn, int d, int E, int tok_per_chunk, int col_blocks,
+                                                               const T* __restrict__ x, const float* __restrict__ dl,
+                                                               float* __restrict__ part) {
+  constexpr int N = EPC<T>::value, U = 4;
+  const int lane = threadIdx.x & 63, q = lane >> 4, i = lane & 15;
+  const int groups = (E + 63) >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  // a workgroup's wavefronts: the expert groups of one column block first (they read the same x)
+  const int cb = wave / groups, eg = wave - cb * groups;
+  if (cb >= col_blocks) return;
+  const int c0 = (cb * 16 + i) * N, e0 = eg * 64 + 4 * i;
+  const int tb = blockIdx.y * tok_per_chunk, te = min(Tn, tb + tok_per_chunk);
+  floatx4 acc[N][4];
+#pragma unroll
+  for (int s = 0; s < N; ++s)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[s][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+  struct Buf {
+    Chunk x[U];
+    float a[U][4];
+  };
+  // the chunk's rows of x and dl as buffers: tokens past its end read as zeros
+  const auto xr = buf_rsrc(x + (size_t)tb * d, (size_t)(te - tb) * d * sizeof(T));
+  const auto gr = buf_rsrc(dl + (size_t)tb * E, (size_t)(te - tb) * E * 4);
+  int xo = (q * d + c0) * (int)sizeof(T), go = (q * E + e0) * 4;
+  auto load = [&](Buf& b) {  // the next 4 U tokens
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      b.x[u] = buf_ld16(xr, xo);
+      if (VEC) {
+        const Chunk v = buf_ld16(gr, e0 < E ? go : kBufPast);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) b.a[u][m] = __uint_as_float(v.w[m]);
+      } else {
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+          b.a[u][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gr, e0 + m < E ? go + 4 * m : kBufPast, 0, 0));
+      }
+      xo += 4 * d * (int)sizeof(T);
+      go += 16 * E;
+    }
+  };
+  auto mul = [&](const Buf& b) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float xf[N];
+      chunk_to_f<T>(b.x[u], xf);
+#pragma unroll
+      for (int s = 0; s < N; ++s)
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+          acc[s][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.a[u][m], xf[s], acc[s][m], 0, 0, 0);
+    }
+  };
+  Buf b0, b1;
+  load(b0);
+  for (int t0 = tb; t0 < te; t0 += 8 * U) {
+    load(b1);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(b0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(b0);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(b1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // register r of lane (q, i), MFMA (s, m): expert 64 eg + 4 (4 q + r) + m, column c0 + s
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int e = eg * 64 + 4 * (4 * q + r) + m;
+      if (e >= E) continue;
+      float* o = part + ((size_t)blockIdx.y * E + e) * d + c0;
+#pragma unroll
+      for (int s = 0; s < N; s += 4)
+        *reinterpret_cast<float4*>(o + s) = float4{acc[s][m][r], acc[s + 1][m][r], acc[s + 2][m][r], acc[s + 3][m][r]};
+    }
+}
+
 // dW_router[o] = sum over chunks of part[chunk][o], in a fixed order: thread (g, o) of a workgroup sums
 // the chunks g, g + 16, g + 32, ... in turn, then the 16 partial sums of an output are added in g order.
 constexpr int RED_G = 16;  // chunk lanes per output
@@ -464,18 +551,25 @@ __global__ __launch_bounds__(256) void route_dw_reduce_kernel(int n4, int nchunk
   }
 }
 
-static int dw_net(int E) { return E <= 16 ? 1 : E <= 32 ? 2 : E <= 64 ? 4 : E <= 128 ? 8 : 16; }
+// Column blocks of a wavefront's 16 chunks (route_dw_wide_kernel).
+static int dw_wide_cols(const moe_desc& d) { return (int)(d.d_model * elem_bytes(d) / 256); }
 
-// Token chunks of the weight-gradient contraction: enough workgroups to fill the chip, chunk sizes a
-// multiple of 32 tokens. A workgroup covers 4 wavefronts x 16 x JJ columns.
-// Workgroups of the partial contraction: about 256 for up to 16 experts, 1024 for more.
+// Token chunks of the weight-gradient contraction, a multiple of 32 tokens each: about 256 workgroups for up to 16
+// experts and 1024 up to 32 (4 wavefronts x 16 x JJ columns each), 1024 wavefronts for
+// more (one per SIMD; 2048 and 4096 take as long or longer here and twice and four times as long in the sum).
 static void route_bwd_chunks(const moe_desc& d, int* nch, int* tpc) {
-  const int net = dw_net(d.n_experts);
-  const int wg_cols = 64 * dw_cols_per_lane(net);
-  const int ncol = (d.d_model + wg_cols - 1) / wg_cols;
+  const int E = d.n_experts;
+  int units, target;
+  if (E > 32) {
+    units = dw_wide_cols(d) * ((E + 63) / 64);
+    target = 1024;
+  } else {
+    const int wg_cols = 64 * dw_cols_per_lane(E <= 16 ? 1 : 2);
+    units = (d.d_model + wg_cols - 1) / wg_cols;
+    target = E <= 16 ? 256 : 1024;
+  }
   const int maxch = (d.T + 31) / 32;
-  const int target = net == 1 ? 256 : 1024;
-  int want = (target + ncol - 1) / ncol;
+  const int want = (target + units - 1) / units;
   int n = want < maxch ? want : maxch;
   if (n < 1) n = 1;
   int per = (d.T + n - 1) / n;
@@ -507,17 +601,25 @@ static hipError_t route_bwd_t(const moe_desc& d, const void* x, const float* log
   float* part = (float*)ws;
   {
     KernelTimer kt("route_dw_partial", s);
-    const int wg_cols = 64 * dw_cols_per_lane(dw_net(E));
-    dim3 grid((d.d_model + wg_cols - 1) / wg_cols, nch);
-#define RB_LAUNCH(NET)                                                                                           \
-  hipLaunchKernelGGL((route_dw_partial_kernel<T, NET, dw_cols_per_lane(NET)>), grid, dim3(256), 0, s, d.T,     \
+    if (E > 32) {
+      const int cb = dw_wide_cols(d);
+      const dim3 grid((cb * ((E + 63) / 64) + 3) / 4, nch);
+      if (E % 4 == 0)
+        hipLaunchKernelGGL((route_dw_wide_kernel<T, true>), grid, dim3(256), 0, s, d.T, d.d_model, E, tpc, cb,
+                           (const T*)x, dl, part);
+      else
+        hipLaunchKernelGGL((route_dw_wide_kernel<T, false>), grid, dim3(256), 0, s, d.T, d.d_model, E, tpc, cb,
+                           (const T*)x, dl, part);
+    } else {
+      const int wg_cols = 64 * dw_cols_per_lane(E <= 16 ? 1 : 2);
+      const dim3 grid((d.d_model + wg_cols - 1) / wg_cols, nch);
+#define RB_LAUNCH(NET)                                                                                       \
+  hipLaunchKernelGGL((route_dw_partial_kernel<T, NET, dw_cols_per_lane(NET)>), grid, dim3(256), 0, s, d.T, \
                      d.d_model, E, tpc, (const T*)x, dl, part)
-    if (E <= 16) RB_LAUNCH(1);
-    else if (E <= 32) RB_LAUNCH(2);
-    else if (E <= 64) RB_LAUNCH(4);
-    else if (E <= 128) RB_LAUNCH(8);
-    else RB_LAUNCH(16);
+      if (E <= 16) RB_LAUNCH(1);
+      else RB_LAUNCH(2);
 #undef RB_LAUNCH
+    }
   }
   {
     KernelTimer kt("route_dw_reduce", s);

@@ -21,23 +21,8 @@
 
 namespace pcmoe {
 
-__device__ __forceinline__ Chunk buf_ld16(__amdgpu_buffer_rsrc_t r, int voff) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
-  Chunk c;
-  c.w[0] = v.x;
-  c.w[1] = v.y;
-  c.w[2] = v.z;
-  c.w[3] = v.w;
-  return c;
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, size_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-
 constexpr int ST_COLS = 64;         // output columns (FWD_GU: 32 gate and 32 up columns) of a K-splitting workgroup
 constexpr int ST_KS = 4;            // its wavefronts
-constexpr int ST_OOR = 0x7fffff00;  // a byte offset past every operand's range: the load returns zeros
 
 // Workgroup -> (group, row chunk of `chunk` rows, column block). Lane l of a wavefront counts the chunks of the groups
 // [l NS, l NS + NS) (one batch of loads), a scan over the lanes finds the lane whose groups hold the tile, and its
@@ -150,7 +135,7 @@ __global__ __launch_bounds__(64 * ST_KS) void stream_split_kernel(GemmArgs p, Pl
   // step r of this wavefront: bytes [128 u, 128 u + 128) of each row, u = r KS + w (zeros past the last unit)
   auto load = [&](int r, Chunk(&wbuf)[NF][2], Chunk(&xbuf)[2]) {
     const int u = r * KS + w;
-    const int vo = u < units ? lane_off + u * 128 : ST_OOR;
+    const int vo = u < units ? lane_off + u * 128 : kBufPast;
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
       const int o = vo + (i % F0) * 16 * K * 2 * (u < units ? 1 : 0);
@@ -249,13 +234,13 @@ __global__ __launch_bounds__(256, 2) void stream_rows_kernel(GemmArgs p, PlanArg
     for (int i = 0; i < NF; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        buf[i][h] = buf_ld16(i < F0 ? wr0 : wr1, u < units ? vo + (i % F0) * 16 * KB + 64 * h : ST_OOR);
+        buf[i][h] = buf_ld16(i < F0 ? wr0 : wr1, u < units ? vo + (i % F0) * 16 * KB + 64 * h : kBufPast);
   };
   auto load_x = [&](int u, Chunk(&buf)[XL]) {
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       const int c = tid + 256 * i;  // rows past the chunk's last one lie past the buffer: zeros
-      buf[i] = buf_ld16(xr, u < units ? (c >> 3) * KB + (c & 7) * 16 + u * 128 : ST_OOR);
+      buf[i] = buf_ld16(xr, u < units ? (c >> 3) * KB + (c & 7) * 16 + u * 128 : kBufPast);
     }
   };
   auto put_x = [&](int stage, const Chunk(&buf)[XL]) {
