@@ -413,10 +413,146 @@ __global__ __launch_bounds__(256) void unpermute_kernel(int Tn, int k, int S, in
   }
 }
 
+// The same hand-back where every expert's router gradient is nonzero (gate weights as the paper states them, without
+// renormalisation): the router term is then a dense [T, E] x [E, d] product, and the ballot walk above would take
+// E / 4 dependent round trips and E d vector multiply-adds per token. Here a wavefront holds 16 tokens x 16 chunks of
+// columns on v_mfma_f32_16x16x4f32: lane (q, i) feeds dlogits[t0 + i][e0 + 4 q + m] and the columns of its chunk of
+// w_router row e0 + 4 q + m (m = 0..3, one 16-byte load each), and ends up with whole chunks of tokens 4 q + r, to which
+// it adds the token's routed and shared rows. Summed as: slots in order, shared experts, then the router term.
+// Bound by the product (T = 8192, d = 2048, E = 256: 8.6 GFLOP of fp32 MFMA, 56 us) beside 300 MB of rows: 147 us, 574
+// by the walk; two token tiles per wavefront, with two wavefronts per SIMD in place of three, 160.
+template <typename T, int KM>
+__global__ __launch_bounds__(256) void unpermute_dense_kernel(int Tn, int k, int S, int E, int cpr, int col_blocks,
+                                                              const Chunk* __restrict__ dxp,
+                                                              const int32_t* __restrict__ s2r,
+                                                              const float* __restrict__ dl,
+                                                              const Chunk* __restrict__ wr, Chunk* __restrict__ dx) {
+  constexpr int N = EPC<T>::value;
+  const int lane = threadIdx.x & 63, q = lane >> 4, i = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int t0 = wave / col_blocks * 16, c = (wave % col_blocks) * 16 + i;  // first token; the lane's chunk
+  if (t0 >= Tn) return;
+  // the tokens' slot maps, kept for the row sums at the end (only this wavefront reads them)
+  __shared__ int slots[4][16 * KM];
+  int* const map = slots[threadIdx.x >> 6];
+  for (int s = lane; s < 16 * KM; s += 64) {
+    const int t = t0 + s / KM, j = s % KM;
+    map[s] = t < Tn && j < k ? s2r[(size_t)t * k + j] : -1;
+  }
+  floatx4 acc[N];
+#pragma unroll
+  for (int s = 0; s < N; ++s) acc[s] = floatx4{0.f, 0.f, 0.f, 0.f};
+  uint32_t top = 0;  // the largest exponent field among the weights read
+  const float* dlr = dl + (size_t)min(t0 + i, Tn - 1) * E + 4 * q;
+  struct Step {
+    Chunk w[4];
+    float g[4];
+  };
+  const bool vec = (E & 3) == 0;  // rows of dlogits 16-byte aligned
+  auto load = [&](int e0, Step& b) {
+    const int e = e0 + 4 * q;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) b.w[m] = e + m < E ? wr[(size_t)(e + m) * cpr + c] : zero_chunk();
+    if (vec) {
+      const float4 v = e < E ? *reinterpret_cast<const float4*>(dlr + e0) : float4{0.f, 0.f, 0.f, 0.f};
+      b.g[0] = v.x;
+      b.g[1] = v.y;
+      b.g[2] = v.z;
+      b.g[3] = v.w;
+    } else {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) b.g[m] = e + m < E ? dlr[e0 + m] : 0.f;
+    }
+  };
+  auto mul = [&](const Step& b) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      float wf[N];
+      chunk_to_f<T>(b.w[m], wf);
+#pragma unroll
+      for (int s = 0; s < N; ++s) {
+        top = max(top, __float_as_uint(wf[s]) & 0x7f800000u);
+        acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.g[m], wf[s], acc[s], 0, 0, 0);
+      }
+    }
+  };
+  Step b0, b1;
+  load(0, b0);
+  for (int e0 = 0; e0 < E; e0 += 32) {
+    load(e0 + 16, b1);
+    mul(b0);
+    load(e0 + 32, b0);
+    mul(b1);
+  }
+  // An expert whose gradient is zero adds nothing, whatever its weights: a product with an infinity or a NaN would.
+  const bool walk = __ballot(top == 0x7f800000u) != 0;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wavefront's map is written
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int t = t0 + 4 * q + r;
+    int rows[KM];
+    Chunk in[KM];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) rows[j] = map[(4 * q + r) * KM + j];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) in[j] = dxp[(size_t)max(rows[j], 0) * cpr + c];  // row 0 in an absent row's place
+    float sum[N], v[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) sum[s] = 0.f;
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+      chunk_to_f<T>(in[j], v);
+#pragma unroll
+      for (int s = 0; s < N; ++s) sum[s] = rows[j] >= 0 ? sum[s] + v[s] : sum[s];
+    }
+    const int ts = min(t, Tn - 1);
+    for (int sh = 0; sh < S; ++sh) {
+      chunk_to_f<T>(dxp[((size_t)Tn * k + (size_t)sh * Tn + ts) * cpr + c], v);
+#pragma unroll
+      for (int s = 0; s < N; ++s) sum[s] += v[s];
+    }
+    if (walk) {
+      for (int e = 0; e < E; ++e) {
+        const float g = dl[(size_t)ts * E + e];
+        if (g == 0.f) continue;
+        chunk_to_f<T>(wr[(size_t)e * cpr + c], v);
+#pragma unroll
+        for (int s = 0; s < N; ++s) sum[s] = fmaf(g, v[s], sum[s]);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < N; ++s) sum[s] += acc[s][r];
+    }
+    if (t < Tn) dx[(size_t)t * cpr + c] = f_to_chunk<T>(sum);
+  }
+}
+
+template <typename T>
+static hipError_t unpermute_dense(const moe_desc& d, int cpr, const void* dxp, const int32_t* s2r, const float* dl,
+                                  const void* wr, void* dx, hipStream_t s) {
+  const int col_blocks = cpr / 16;  // d_model is a multiple of 128: whole blocks of 16 chunks
+  const long waves = (long)((d.T + 15) / 16) * col_blocks;
+  auto go = [&](auto km) {
+    hipLaunchKernelGGL((unpermute_dense_kernel<T, decltype(km)::value>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0,
+                       s, d.T, d.top_k, d.n_shared, d.n_experts, cpr, col_blocks, (const Chunk*)dxp, s2r, dl,
+                       (const Chunk*)wr, (Chunk*)dx);
+  };
+  if (d.top_k <= 2) go(std::integral_constant<int, 2>{});
+  else if (d.top_k <= 4) go(std::integral_constant<int, 4>{});
+  else go(std::integral_constant<int, 8>{});
+  return hipGetLastError();
+}
+
 hipError_t launch_permute_bwd(const moe_desc& d, const void* dxp, const int32_t* s2r, const float* dl,
                               const void* wr, void* dx, hipStream_t s) {
   const int cpr = (int)(d.d_model * elem_bytes(d) / 16);
   KernelTimer kt("unpermute", s);
+  // Without renormalisation every expert's gradient is nonzero. Up to 8 experts the first round trip of the walk takes
+  // most of them (9 experts, T = 777, d = 4096: 13.6 us by the walk, 12.9 by the product; 16, T = 16384: 83 and 71).
+  if (dl && !d.renormalize && d.n_experts > 8)
+    return d.dtype == MOE_BF16 ? unpermute_dense<bf16>(d, cpr, dxp, s2r, dl, wr, dx, s)
+                               : unpermute_dense<float>(d, cpr, dxp, s2r, dl, wr, dx, s);
   batch_dispatch(d.top_k, d.n_shared, dl != nullptr, [&](auto km, auto sm, auto has_dl) {
     constexpr int KM = decltype(km)::value, SM = decltype(sm)::value;
     constexpr bool DL = decltype(has_dl)::value;

@@ -1,0 +1,79 @@
+"""The router's adjoint without renormalisation (every expert's gradient is nonzero): the dense router term of the
+input-gradient hand-back and the weight gradient of more than 32 experts, where token tiles (16), expert steps (16, 64)
+and 32-token chunks end, against fp64 sums of the same inputs."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_02965_amd import pcmoe as P
+from gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # T, d, E, k, shared, dtype
+    (1, 128, 9, 2, 0, "bf16"), (15, 256, 16, 3, 1, "bf16"), (17, 128, 33, 8, 2, "f32"), (33, 384, 50, 5, 3, "bf16"),
+    (64, 128, 64, 1, 0, "f32"), (129, 640, 65, 4, 0, "bf16"), (1030, 256, 256, 8, 0, "bf16"),
+    (515, 128, 255, 6, 1, "f32"),
+]
+
+
+def _inputs(T, d, E, k, S, dtype, seed=5):
+    g = torch.Generator().manual_seed(seed)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    n = lambda *s: torch.randn(*s, generator=g)
+    x, wr, dxp = n(T, d).to(dt), (n(E, d) * d ** -0.5).to(dt), n(T * k + S * T, d).to(dt)
+    idx = torch.stack([torch.randperm(E, generator=g)[:k] for _ in range(T)]).int()
+    s2r = torch.randperm(T * k, generator=g).int()
+    return x, wr, dxp, idx, s2r, n(T, E), n(T, k)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "T{}_d{}_E{}_k{}_S{}_{}".format(*c))
+def test_dense_router_adjoint(case):
+    T, d, E, k, S, dtype = case
+    log(f"[dense router] {case}")
+    x, wr, dxp, idx, s2r, logits, dgate = _inputs(*case)
+    desc = P.make_desc(T, d, 128, E, k, 0, E, S, False, dtype)
+    dev = lambda t: t.cuda().contiguous()
+    dl, dwr = torch.empty(T, E, device="cuda"), torch.empty(E, d, device="cuda")
+    dx = torch.empty(T, d, device="cuda", dtype=x.dtype)
+    ws = torch.empty(max(P.moe_workspace_size(desc, P.MOE_WS_ROUTE_BWD), 1), dtype=torch.uint8, device="cuda")
+    topk_w = torch.softmax(logits.double(), 1).gather(1, idx.long()).float()
+    P.moe_route_bwd(desc, dev(x), dev(logits), dev(idx), dev(topk_w), dev(dgate), dl, dwr, ws, ws.numel())
+    P.moe_permute_bwd(desc, dev(dxp), dev(s2r), dl, dev(wr), dx)
+    torch.cuda.synchronize()
+    p = torch.softmax(logits.double(), 1)
+    gg = torch.zeros(T, E, dtype=torch.float64).scatter_(1, idx.long(), dgate.double())
+    ref_dl = p * (gg - (p * gg).sum(1, keepdim=True))
+    got_dl = dl.cpu().double()
+    # fp32 exp, division and one 64-lane sum: a few ulp of the largest entry
+    assert (got_dl - ref_dl).abs().max() <= 1e-5 * ref_dl.abs().max()
+    # the products take the gradients the kernel was given
+    ref_dw = got_dl.t() @ x.double()
+    assert (dwr.cpu().double() - ref_dw).abs().max() <= 1e-5 * ref_dw.abs().max()   # fp32 sums over T
+    rows = dxp.double()
+    ref_dx = rows[s2r.long()].view(T, k, d).sum(1) + got_dl @ wr.double()
+    for s in range(S):
+        ref_dx = ref_dx + rows[T * k + s * T:T * k + (s + 1) * T]
+    tol = 2 ** -8 if dtype == "bf16" else 1e-5   # one rounding to bf16 of the fp32 sum
+    assert (dx.cpu().double() - ref_dx).abs().max() <= tol * ref_dx.abs().max()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_zero_gradient_skips_infinite_weights(dtype):
+    """An expert whose gradient is zero contributes nothing even where its router row is infinite or NaN."""
+    T, d, E, k = 40, 256, 20, 2
+    log(f"[dense router] infinite row {dtype}")
+    x, wr, dxp, idx, s2r, _, _ = _inputs(T, d, E, k, 0, dtype)
+    dl = torch.randn(T, E)
+    dl[:, 7] = 0.0
+    dl[3, 11] = 0.0
+    ref = dxp.double()[s2r.long()].view(T, k, d).sum(1) + dl.double() @ wr.double()
+    wr[7] = float("inf")
+    wr[7, ::2] = float("nan")
+    desc = P.make_desc(T, d, 128, E, k, 0, E, 0, False, dtype)
+    dx = torch.empty(T, d, device="cuda", dtype=x.dtype)
+    P.moe_permute_bwd(desc, dxp.cuda(), s2r.cuda(), dl.cuda(), wr.cuda(), dx)
+    torch.cuda.synchronize()
+    tol = 2 ** -8 if dtype == "bf16" else 1e-5
+    assert (dx.cpu().double() - ref).abs().max() <= tol * ref.abs().max()
+    assert np.isfinite(dx.float().cpu().numpy()).all()
