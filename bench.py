@@ -194,7 +194,7 @@ def hbm_steps(cfg, n_routed, kernels):
     """Achieved HBM bandwidth of the bandwidth-bound steps from their algorithmic bytes per launch
     (s = element bytes, N = routed rows, S = shared experts):
       router forward   T*d*s + E*d*s + 4*T*E + 8*T*k   (x and W_r read; logits, top-k indices and weights written)
-      permute          T*d*s + N*d*s + 8*T*k           (histogram, scatter and gather launches together)
+      permute          T*d*s + N*d*s + 8*T*k           (histogram, scatter and gather, or their one launch)
       combine          N*d*s + T*d*s + S*T*d*s + 8*T*k
       combine backward T*d*s + 2*N*d*s + 8*T*k
       unpermute        N*d*s + T*d*s + S*T*d*s + 4*T*k
@@ -204,7 +204,8 @@ def hbm_steps(cfg, n_routed, kernels):
     T, d, k, E, S, N = cfg.T, cfg.d, cfg.k, cfg.E, cfg.n_shared, n_routed
     table = {
         "route_fwd": (("route_fwd",), T * d * s + E * d * s + 4 * T * E + 8 * T * k),
-        "permute": (("permute_hist", "permute_scatter", "permute_gather"), T * d * s + N * d * s + 8 * T * k),
+        "permute": (("permute_fused",) if "permute_fused" in kernels else
+                    ("permute_hist", "permute_scatter", "permute_gather"), T * d * s + N * d * s + 8 * T * k),
         "combine": (("combine",), N * d * s + T * d * s + S * T * d * s + 8 * T * k),
         "combine_bwd": (("combine_bwd",), T * d * s + 2 * N * d * s + 8 * T * k),
         "unpermute": (("unpermute",), N * d * s + T * d * s + S * T * d * s + 4 * T * k),

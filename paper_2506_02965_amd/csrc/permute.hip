@@ -9,6 +9,7 @@
 //      counts and offsets), then each wavefront ranks its 64 slots with ballots (lanes holding the
 //      same expert form a peer mask; rank = popcount of lower peers), waves in order.
 //   3. gather: one wavefront per token reads its row once and writes its k destinations.
+// A few thousand slots take one launch that does all three (perm_small_kernel).
 #include "pcmoe_internal.h"
 
 namespace pcmoe {
@@ -189,6 +190,113 @@ __global__ __launch_bounds__(256) void perm_gather_kernel(int Tn, int k, int cpr
   }
 }
 
+// The whole dispatch in one launch for a few thousand slots, where three launches cost more than their work. Every
+// workgroup of 16 wavefronts ranks all the slots itself (wavefront w the slots [64 ITERS w, 64 ITERS (w + 1)), one ballot
+// pass, stable), so no workgroup waits for another; it then gathers its own tokens, whose first chunks are loaded ahead
+// of the ranking. Workgroup 0 also writes counts, offsets and both maps. Bound by the launch and the ranking's chain of
+// ballots: 6 to 1,800 slots 13.6-15.8 -> 8.2-9.5 us a call (the call's host side is most of the rest).
+constexpr int PS_WAVES = 16;
+template <int ITERS>
+__global__ __launch_bounds__(64 * PS_WAVES) void perm_small_kernel(const int32_t* __restrict__ idx, int Tn, int k, int lb,
+                                                                   int lc, int nbits, int cpr,
+                                                                   const Chunk* __restrict__ x,
+                                                                   int32_t* __restrict__ counts,
+                                                                   int32_t* __restrict__ offsets,
+                                                                   int32_t* __restrict__ r2s, int32_t* __restrict__ s2r,
+                                                                   Chunk* __restrict__ xp) {
+  constexpr int SLOTS = 64 * ITERS * PS_WAVES, CPL = 4;
+  __shared__ int row_of[SLOTS];          // the slots' rows (-1: hosted elsewhere)
+  __shared__ int wcnt[PS_WAVES][256];    // per wavefront and expert: slots, then the first of its rows
+  __shared__ int wsum[4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nslots = Tn * k;
+  const int wave = blockIdx.x * PS_WAVES + w, nwaves = gridDim.x * PS_WAVES;
+  Chunk xv[CPL];
+  auto load_x = [&](int t, int c0) {
+#pragma unroll
+    for (int u = 0; u < CPL; ++u)
+      xv[u] = t < Tn && c0 + 64 * u < cpr ? x[(size_t)t * cpr + c0 + 64 * u] : zero_chunk();
+  };
+  int v_of[ITERS], rank[ITERS];
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int a = (w * ITERS + it) * 64 + lane;
+    const int v = (a < nslots) ? idx[a] - lb : -1;
+    v_of[it] = (v >= 0 && v < lc) ? v : -1;
+  }
+  load_x(wave, lane);
+  for (int i = lane; i < lc; i += 64) wcnt[w][i] = 0;
+  __syncthreads();
+  const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int v = v_of[it];
+    const uint64_t peers = peer_mask(v < 0 ? 0 : v, v >= 0, nbits);
+    rank[it] = v >= 0 ? wcnt[w][v] + __popcll(peers & lt) : 0;
+    asm volatile("" ::: "memory");  // the count is read before the peers' first lane raises it
+    if (v >= 0 && (peers & lt) == 0) wcnt[w][v] += __popcll(peers);
+  }
+  __syncthreads();
+  // expert e = thread: its rows over all wavefronts, the exclusive prefix over experts, and each wavefront's first row
+  int tot = 0, incl = 0;
+  if (tid < 256) {
+    if (tid < lc) {
+#pragma unroll
+      for (int ww = 0; ww < PS_WAVES; ++ww) tot += wcnt[ww][tid];
+    }
+    incl = tot;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += o;
+    }
+    if (lane == 63) wsum[w] = incl;
+  }
+  __syncthreads();
+  const int nloc = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  if (tid < lc) {
+    int r = incl - tot;
+    for (int i = 0; i < w; ++i) r += wsum[i];
+    if (blockIdx.x == 0) {
+      counts[tid] = tot;
+      offsets[tid] = r;
+      if (tid == 0) offsets[lc] = nloc;
+    }
+#pragma unroll
+    for (int ww = 0; ww < PS_WAVES; ++ww) {
+      const int c = wcnt[ww][tid];
+      wcnt[ww][tid] = r;
+      r += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int a = (w * ITERS + it) * 64 + lane, v = v_of[it];
+    const int pos = v >= 0 ? wcnt[w][v] + rank[it] : -1;
+    row_of[a] = pos;
+    if (blockIdx.x == 0 && a < nslots) {
+      s2r[a] = pos;
+      if (pos >= 0) r2s[pos] = a;
+      if (a >= nloc) r2s[a] = -1;  // rows beyond the hosted ones have no slot
+    }
+  }
+  __syncthreads();
+  for (int t = wave; t < Tn; t += nwaves) {
+    for (int c0 = lane; c0 < cpr; c0 += 64 * CPL) {
+      if (t != wave || c0 != lane) load_x(t, c0);
+      for (int j = 0; j < k; ++j) {
+        const int row = __builtin_amdgcn_readfirstlane(row_of[t * k + j]);
+        if (row < 0) continue;
+#pragma unroll
+        for (int u = 0; u < CPL; ++u)
+          if (c0 + 64 * u < cpr) xp[(size_t)row * cpr + c0 + 64 * u] = xv[u];
+      }
+    }
+  }
+}
+
 static int nbits_for(int lc) {
   int nb = 0;
   while ((1 << nb) < lc) ++nb;
@@ -238,6 +346,18 @@ hipError_t launch_permute(const moe_desc& d, const int32_t* idx, const void* x, 
   const int nblk = (nslots + PM_SLOTS - 1) / PM_SLOTS;
   const int lc = d.local_count;
   int32_t* blk_counts = (int32_t*)ws;
+  // One launch as long as every workgroup's ranking of all the slots costs less than the launches it saves: up to 4,096
+  // slots, 8,192 where the experts take at most 5 ballots each (us, three launches and one: 4,096 slots 13.8-17.3 and
+  // 8.2-12.9; 8,192 slots of 8 and 16 experts 25.0 and 21.4, 14.1 and 11.7, of 256 experts 18.8 and 21.1; 16,384 slots
+  // 17.5 and 31.8).
+  if (nslots <= 4096 || (nslots <= 8192 && lc <= 32)) {
+    KernelTimer kt("permute_fused", s);
+    const int cpr = (int)(d.d_model * elem_bytes(d) / 16);
+    auto kern = nslots <= 1024 ? perm_small_kernel<1> : nslots <= 4096 ? perm_small_kernel<4> : perm_small_kernel<8>;
+    hipLaunchKernelGGL(kern, dim3((d.T + PS_WAVES - 1) / PS_WAVES), dim3(64 * PS_WAVES), 0, s, idx, d.T, d.top_k,
+                       d.local_begin, lc, nbits_for(lc), cpr, (const Chunk*)x, counts, offsets, r2s, s2r, (Chunk*)xp);
+    return hipGetLastError();
+  }
   {
     KernelTimer kt("permute_hist", s);
     hipLaunchKernelGGL(perm_hist_kernel, dim3(nblk), dim3(256), lc * sizeof(int), s, idx, nslots, d.local_begin, lc,
