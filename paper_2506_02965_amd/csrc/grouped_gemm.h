@@ -324,8 +324,9 @@ __global__ __launch_bounds__(512) void tile_plan_kernel(PlanArgs a);
 // Few rows per expert (bf16): the forward's contractions with the weights streamed straight into registers. mt = 0: the
 // LDS tiles are the better choice (their grid has tile_grid workgroups).
 struct StreamPick {
-  int mt;  // 16-row blocks per workgroup
-  int nf;  // FWD_DOWN: 16-column blocks per wavefront
+  int mt;     // 16-row blocks per workgroup
+  int nf;     // 16-row blocks of weights per wavefront
+  int depth;  // K steps of weights in registers
 };
 StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid);
 hipError_t stream_gate_up(const moe_desc& d, const StreamPick& k, const GemmArgs& a, const PlanArgs& plan,

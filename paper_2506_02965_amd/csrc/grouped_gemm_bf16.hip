@@ -1285,7 +1285,7 @@ hipError_t launch_ffn_fwd(const moe_desc& d, const void* x, const void* xp, cons
   int* tickets = (int*)((char*)saved + saved_plan_offset(d) + align256(plan_bytes(d)));
   const Plan pl = plan_at(d, (char*)saved + saved_plan_offset(d));
   const PlanArgs pa = plan_args(d, offsets, pl, tickets, 2);
-  StreamPick gu{0, 0}, down{0, 0};
+  StreamPick gu{0, 0, 0}, down{0, 0, 0};
   if (d.dtype == MOE_BF16 && dynamic_tiles() != 2) {
     if (forced_shape(FWD_GU) < 0) gu = stream_pick(d, FWD_GU, mtile_bound2(d, 256) * ((2 * d.d_ff + 255) / 256));
     if (forced_shape(FWD_DOWN) < 0) down = stream_pick(d, FWD_DOWN, mtile_bound2(d, 192) * ((d.d_model + 255) / 256));

@@ -348,10 +348,13 @@ static hipError_t run_rows(const moe_desc& d, const GemmArgs& a, const PlanArgs&
 //     previous one 5-50% above it);
 //   * past 100 rows the LDS tiles take over (at 128 rows they are 0-25% faster, at 64 rows 0-60% slower), except
 //     where their grid would leave half the CUs or more idle: the chunks are 10-60% faster there up to 200 rows.
-// FWD_DOWN at 33 rows and more takes 128 columns per workgroup as long as that leaves one workgroup per CU (at 64 rows
-// 16% faster with d = 4096, 14% slower with d = 1024 and 16 experts).
+// FWD_DOWN at 25 rows and more takes 128 columns per workgroup as long as that leaves one workgroup per CU (at 64 rows
+// 16% faster with d = 4096, 14% slower with d = 1024 and 16 experts). A grid of few workgroups is bound by the round
+// trips of each: 64-row chunks in place of 128 below 3/4 of a workgroup per CU (f = 8192, d = 1536, 5 groups, 64 rows:
+// 83 -> 60 us), and 8 steps in flight in place of 4 up to two per CU (f = 8192, 12 rows: 55 -> 49 us; f = 2816, d = 1024:
+// 25 -> 22; 128 experts, d = 512, are 10% slower with 8).
 StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid) {
-  StreamPick none{0, 0}, split{1, 1};
+  const StreamPick none{0, 0, 0}, split{1, 1, 2};
   if (d.dtype != MOE_BF16) return none;
   const int G = d.local_count + d.n_shared;
   const double rows = ((double)d.T * d.top_k * d.local_count / d.n_experts + (double)d.T * d.n_shared) / G;
@@ -359,9 +362,12 @@ StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid) {
   const long split_wgs = chunk_bound(d, 16) * (cols / (kind == FWD_GU ? ST_COLS / 2 : ST_COLS));
   if (rows <= 8 && split_wgs <= 5L * cus) return split;
   if (rows > (tile_grid <= cus / 2 ? 200 : 100)) return none;
-  const int mt = rows <= 24 ? 2 : rows <= 50 ? 4 : 8;
-  const bool wide = kind == FWD_DOWN && mt > 2 && chunk_bound(d, 16 * mt) * (cols / 128) >= cus;
-  return StreamPick{mt, wide ? 2 : 1};
+  int mt = rows <= 24 ? 2 : rows <= 50 ? 4 : 8;
+  if (kind == FWD_GU) return StreamPick{mt, 2, mt == 8 ? 2 : 4};
+  const auto wgs = [&](int m, int nf) { return chunk_bound(d, 16 * m) * (cols / (64 * nf)); };
+  if (mt == 8 && wgs(8, 1) < cus * 3 / 4) mt = 4;
+  const int nf = mt > 2 && wgs(mt, 2) >= cus ? 2 : 1;
+  return StreamPick{mt, nf, mt < 8 && nf == 1 && wgs(mt, 1) <= 2L * cus && d.d_ff >= 1024 ? 8 : 4};
 }
 
 hipError_t stream_gate_up(const moe_desc& d, const StreamPick& k, const GemmArgs& a, const PlanArgs& plan,
@@ -377,10 +383,13 @@ hipError_t stream_down(const moe_desc& d, const StreamPick& k, const GemmArgs& a
   const PlanArgs none{};
   switch (k.mt) {
     case 1: return run_split<FWD_DOWN>(d, a, none, s, name);
-    case 2: return run_rows<FWD_DOWN, 2, 1, 4>(d, a, none, s, name);
+    case 2:
+      return k.depth == 8 ? run_rows<FWD_DOWN, 2, 1, 8>(d, a, none, s, name)
+                          : run_rows<FWD_DOWN, 2, 1, 4>(d, a, none, s, name);
     case 4:
-      return k.nf == 2 ? run_rows<FWD_DOWN, 4, 2, 4>(d, a, none, s, name)
-                       : run_rows<FWD_DOWN, 4, 1, 4>(d, a, none, s, name);
+      return k.nf == 2      ? run_rows<FWD_DOWN, 4, 2, 4>(d, a, none, s, name)
+             : k.depth == 8 ? run_rows<FWD_DOWN, 4, 1, 8>(d, a, none, s, name)
+                            : run_rows<FWD_DOWN, 4, 1, 4>(d, a, none, s, name);
     default:
       return k.nf == 2 ? run_rows<FWD_DOWN, 8, 2, 4>(d, a, none, s, name)
                        : run_rows<FWD_DOWN, 8, 1, 4>(d, a, none, s, name);

@@ -34,8 +34,13 @@ CASES = {
     # <= 50: 64-row chunks, one and two column blocks per wavefront of the down projection
     "rows64": _case(300, 256, 640, 16, [0, 63, 64, 65, 129, 1], 76, n_shared=1),
     "rows64_wide": _case(640, 1024, 128, 40, [0, 63, 64, 65, 130], 77),
+    # few workgroups and a long K: 8 steps in flight, 32- and 64-row chunks (the latter in place of 128)
+    "rows32_deep": _case(60, 256, 1152, 8, [0, 31, 33, 1], 83),
+    "rows64_deep": _case(150, 256, 1024, 8, [0, 63, 64, 65, 1], 84),
+    "rows64_few": _case(300, 256, 1408, 8, [0, 63, 129, 1], 85),
     # <= 100 (and up to 200 where the tile grid is small): 128-row chunks
     "rows128": _case(515, 384, 256, 8, [0, 127, 128, 129, 257, 1], 78),
+    "rows128_narrow": _case(400, 1024, 128, 12, [0, 127, 128, 129, 1], 86),
     "rows128_wide": _case(1100, 1024, 128, 40, [0, 127, 128, 129, 258], 79),
 }
 
