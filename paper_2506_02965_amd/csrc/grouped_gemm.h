@@ -332,6 +332,9 @@ StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid);
 hipError_t stream_gate_up(const moe_desc& d, const StreamPick& k, const GemmArgs& a, const PlanArgs& plan,
                           hipStream_t s, const char* name);
 hipError_t stream_down(const moe_desc& d, const StreamPick& k, const GemmArgs& a, hipStream_t s, const char* name);
+// ... and dX (0: the LDS tiles are the better choice; else 16-row blocks per workgroup)
+int stream_dx_pick(const moe_desc& d);
+hipError_t stream_dx(const moe_desc& d, int mt, const GemmArgs& a, hipStream_t s, const char* name);
 
 // fp32 path; pre64: m-tile prefix for 64-row tiles, order: groups by decreasing row count
 hipError_t ffn_fwd_f32(const moe_desc& d, const void* x, const void* xp, const int32_t* offsets, const void* wg,

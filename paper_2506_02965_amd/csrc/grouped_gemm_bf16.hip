@@ -1339,13 +1339,18 @@ hipError_t launch_ffn_bwd(const moe_desc& d, const void* x, const void* xp, cons
   const Prep dh = prep_ragged<BWD_DH>(d, a, pl, d.d_ff), wd_ = prep_wgrad<WG_DOWN>(d, a_wd, pl, d.d_model, d.d_ff);
   const Prep dx = prep_ragged<BWD_DX>(d, a_dx, pl, d.d_model, pair_enabled()),
              wgu = prep_wgrad<WG_GU>(d, a_wgu, pl, 2 * d.d_ff, d.d_model);
+  const int sdx = dynamic_tiles() != 2 && pair_enabled() && forced_shape(BWD_DX) < 0 ? stream_dx_pick(d) : 0;
   // the counters are read only by paired launches that claim tiles at run time: cleared (one launch) only then
-  if (dynamic_tiles() && (pair_claims(dh, wd_) || pair_claims(dx, wgu))) {
+  if (dynamic_tiles() && (pair_claims(dh, wd_) || (!sdx && pair_claims(dx, wgu)))) {
     hipLaunchKernelGGL(zero_tickets_kernel, dim3(1), dim3(64), 0, s, tickets, 16);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
   hipError_t e = run_pair<BWD_DH, WG_DOWN>(dh, wd_, dynamic_tiles() ? tickets : nullptr, s, "gemm_bwd_dh+wgrad_down");
   if (e != hipSuccess) return e;
+  if (sdx) {
+    if ((e = stream_dx(d, sdx, a_dx, s, kKindName[BWD_DX])) != hipSuccess) return e;
+    return run<WG_GU>(wgu, s);
+  }
   return run_pair<BWD_DX, WG_GU>(dx, wgu, dynamic_tiles() ? tickets + 8 : nullptr, s, "gemm_bwd_dx+wgrad_gate_up");
 }
 

@@ -306,6 +306,109 @@ __global__ __launch_bounds__(256, 2) void stream_rows_kernel(GemmArgs p, PlanArg
   }
 }
 
+// dX = dG W_gate + dU W_up of few rows, where the LDS tiles of d columns are too few for the length of K = 2 f. K is the
+// slow dimension of the weights here, so a wavefront reads 32 k-rows x 128 columns per step, each load 256 contiguous
+// bytes of 4 rows, and turns a lane's 8 k x 8 n block into 8 MFMA operands with 32 byte permutes: operand s of lane (q, i)
+// holds column 8 i + s, k = 8 q .. 8 q + 7. A lane's accumulators of one row are then 8 consecutive columns. The DX_KS
+// wavefronts split K and their partial sums meet in LDS, in wavefront order, 64 columns of 16 rows at a time.
+constexpr int DX_KS = 8, DX_COLS = 128;
+template <int MT>
+__global__ __launch_bounds__(64 * DX_KS, 2) void stream_dx_kernel(GemmArgs p, int n_blocks) {
+  constexpr int KS = DX_KS, PITCH = 64 + 4, D = 3;  // D: steps of weights in registers
+  __shared__ __align__(16) float red[KS * 16 * PITCH];
+  StreamTile t;
+  if (!stream_decode(p, blockIdx.x, 16 * MT, n_blocks, t)) return;
+  const int lane = threadIdx.x & 63, q = lane >> 4, li = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KB = 4 * p.f, NB = 2 * p.d;  // bytes of a row of dG|dU and of a weight matrix
+  const bool routed = t.g < p.Eloc;
+  const size_t rs = routed ? (size_t)t.row0 : (size_t)p.rows_cap + (size_t)(t.g - p.Eloc) * p.T;
+  const char* xb = (const char*)p.dgu + rs * KB;
+  const int m0 = t.ch * 16 * MT, m_rows = min(t.rows - m0, 16 * MT);
+  const auto xr = buf_rsrc(xb + (size_t)m0 * KB, (size_t)m_rows * KB);
+  const int n0 = t.nb * DX_COLS;
+  const size_t wsz = (size_t)p.d * p.f * 2;
+  const char* w0 = (const char*)p.wg + t.g * wsz;
+  const char* w1 = (const char*)p.wu + t.g * wsz;
+
+  const int half = p.f / 32, units = 2 * half, rounds = (units + KS - 1) / KS;  // units >= half are W_up rows
+  floatx4 acc[8][MT];
+#pragma unroll
+  for (int s = 0; s < 8; ++s)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[s][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+  Chunk wb[D][8], xv[D][MT];
+  // step r of this wavefront: k-rows 32 u .. 32 u + 31, u = r KS + w (zeros past the last)
+  auto load = [&](int r, Chunk(&wbuf)[8], Chunk(&xbuf)[MT]) {
+    const int u = r * KS + w;
+    const bool up = u >= half;
+    const auto wr = buf_rsrc(up ? w1 : w0, wsz);
+    const int vo = u < units ? ((up ? u - half : u) * 32 + 8 * q) * NB + (n0 + 8 * li) * 2 : kBufPast;
+    const int xo = u < units ? li * KB + u * 64 + q * 16 : kBufPast;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xbuf[m] = buf_ld16(xr, u < units ? xo + m * 16 * KB : kBufPast);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) wbuf[j] = buf_ld16(wr, u < units ? vo + j * NB : kBufPast);
+  };
+  auto mul = [&](const Chunk(&wbuf)[8], const Chunk(&xbuf)[MT]) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      // halves (s & 1) of dword s / 2 of rows 2 j and 2 j + 1
+      Chunk a;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        a.w[j] = __builtin_amdgcn_perm(wbuf[2 * j + 1].w[s / 2], wbuf[2 * j].w[s / 2],
+                                       (s & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        acc[s][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                            __builtin_bit_cast(bf16x8, xbuf[m]), acc[s][m], 0, 0, 0);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < D; ++s) {
+    load(s, wb[s], xv[s]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  for (int r = 0; r < rounds; r += D) {
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      mul(wb[s], xv[s]);  // (steps past the last are zeros)
+      __builtin_amdgcn_sched_barrier(0);
+      load(r + s + D, wb[s], xv[s]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // Sum and store. Round (m, h): rows 16 m .. 16 m + 15, the 8-column blocks 4 q + 2 h and 4 q + 2 h + 1; thread ->
+  // (row, 4 columns).
+  const int rr = threadIdx.x >> 4, c = (threadIdx.x & 15) * 4;  // (threads past 16 rows only write partials)
+  const int col = n0 + 8 * (4 * ((c & 31) >> 3) + (c >> 5)) + (c & 7);
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    if (16 * m >= m_rows) break;  // uniform
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (m + h) __syncthreads();
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        float* o = &red[(w * 16 + li) * PITCH + 32 * b + 8 * q];
+        const int r = 2 * h + b;
+        *reinterpret_cast<floatx4*>(o) = floatx4{acc[0][m][r], acc[1][m][r], acc[2][m][r], acc[3][m][r]};
+        *reinterpret_cast<floatx4*>(o + 4) = floatx4{acc[4][m][r], acc[5][m][r], acc[6][m][r], acc[7][m][r]};
+      }
+      __syncthreads();
+      if (rr < 16 && 16 * m + rr < m_rows) {
+        floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) v += *reinterpret_cast<const floatx4*>(&red[(k * 16 + rr) * PITCH + c]);
+        const size_t row = rs + m0 + 16 * m + rr;
+        store_out(p, row, col + 16 * h, v);
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------------- host side
 
 // Upper bound on the row chunks: each routed chunk holds at least one row, and all but one per group are full.
@@ -394,6 +497,29 @@ hipError_t stream_down(const moe_desc& d, const StreamPick& k, const GemmArgs& a
       return k.nf == 2 ? run_rows<FWD_DOWN, 8, 2, 4>(d, a, none, s, name)
                        : run_rows<FWD_DOWN, 8, 1, 4>(d, a, none, s, name);
   }
+}
+
+// The LDS tiles of dX take about 1.25 us per 64-deep step (the round trip of a K-tile's loads), 2 f / 64 of them in a
+// chain, beside the weight gradient's stores in the same launch; streamed, dX reads its weights at the memory's rate, but
+// before those stores. So it is streamed where the chain is longer than both together: us, paired tiles and dX +
+// dW_gate, dW_up streamed: d = 1536, f = 8192, 5 groups, 16 rows: 320 and 175; d = 1024, f = 2816, 16 groups, 6 rows: 116
+// and 90, 110 rows: 146 and 140; d = 4096, f = 14336, 8 groups: 716 and 856; d = 3072, f = 768, 32 groups: 139 and 141;
+// d = 256, f = 512, 8 groups: 17 and 20. 16-row chunks up to 24 rows, 32 above (32 rows: 112 and 101 with d = 1024).
+// (The same kernel for dG|dU lost to the paired tiles in every one of these.)
+int stream_dx_pick(const moe_desc& d) {
+  const int G = d.local_count + d.n_shared;
+  const double rows = ((double)d.T * d.top_k * d.local_count / d.n_experts + (double)d.T * d.n_shared) / G;
+  const double chain_us = 1.25 * (2.0 * d.d_ff / 64), bytes = 8.0 * d.d_ff * d.d_model * G;
+  if (rows > 128 || chain_us <= 1.2 * bytes / 5.2e6 + 20) return 0;
+  return rows <= 24 ? 1 : 2;
+}
+hipError_t stream_dx(const moe_desc& d, int mt, const GemmArgs& a, hipStream_t s, const char* name) {
+  const int n_blocks = d.d_model / DX_COLS;
+  const dim3 grid(grid_of(chunk_bound(d, 16 * mt) * n_blocks));
+  KernelTimer kt(name, s);
+  if (mt == 1) hipLaunchKernelGGL(stream_dx_kernel<1>, grid, dim3(64 * DX_KS), 0, s, a, n_blocks);
+  else hipLaunchKernelGGL(stream_dx_kernel<2>, grid, dim3(64 * DX_KS), 0, s, a, n_blocks);
+  return hipGetLastError();
 }
 
 }  // namespace pcmoe

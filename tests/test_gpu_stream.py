@@ -45,6 +45,14 @@ CASES = {
 }
 
 
+# a long d_ff beside few columns: the streamed dX, 16- and 32-row chunks
+CASES.update({
+    "dx16": _case(24, 256, 2816, 4, [0, 16, 17], 87),
+    "dx32": _case(65, 128, 2944, 4, [65, 33, 0], 88, n_shared=1),
+    "dx_mid": _case(150, 384, 2816, 6, [31, 32, 0, 129], 89),
+})
+
+
 def forced(inp, counts):
     T = inp.cfg.T
     assert sum(counts) == 2 * T and max(counts) <= T
