@@ -77,6 +77,9 @@ __global__ __launch_bounds__(256) void combine_kernel(int Tn, int k, int S, int 
   }
 }
 
+// The y_perm rows are read here for the last time, and nearly as many bytes are written beside them: read non-temporal,
+// they leave the last-level cache to the writes (T = 16384, d = 2048, top-6: 159 -> 144 us; T = 8192, top-8: 110 -> 94;
+// the same for the combine's reads, which this kernel repeats, or the hand-back's, moved the time to the next kernel).
 template <typename T, int KM, int CPL>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(int Tn, int k, int cpr, const Chunk* __restrict__ dy,
                                                           const Chunk* __restrict__ yp,
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(int Tn, int k, int cpr
       for (int j = 0; j < KM; ++j)
 #pragma unroll
         for (int u = 0; u < CPL; ++u)
-          in[j][u] = (rows[j] >= 0 && c0 + 64 * u < cpr) ? yp[(size_t)rows[j] * cpr + c0 + 64 * u] : zero_chunk();
+          in[j][u] = (rows[j] >= 0 && c0 + 64 * u < cpr) ? ld_chunk_nt(yp + (size_t)rows[j] * cpr + c0 + 64 * u) : zero_chunk();
 #pragma unroll
       for (int u = 0; u < CPL; ++u) {
         const int c = c0 + 64 * u;

@@ -77,6 +77,17 @@ __device__ __forceinline__ void st_chunk_nt(void* p, const Chunk& c) {
   const u32x4 v = {c.w[0], c.w[1], c.w[2], c.w[3]};
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
+// ... and a load marked so: for rows read for the last time.
+__device__ __forceinline__ Chunk ld_chunk_nt(const void* p) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  Chunk c;
+  c.w[0] = v.x;
+  c.w[1] = v.y;
+  c.w[2] = v.z;
+  c.w[3] = v.w;
+  return c;
+}
 // 16 bytes from a buffer of `bytes` bytes (below 2^31 - 256, p wave-uniform) at byte offset voff: zeros at and past the
 // end, so kBufPast skips a load without a branch.
 constexpr int kBufPast = 0x7fffff00;
