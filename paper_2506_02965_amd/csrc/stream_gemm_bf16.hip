@@ -450,7 +450,10 @@ static hipError_t run_rows(const moe_desc& d, const GemmArgs& a, const PlanArgs&
 //   * up to 24, 50 and 100 rows: 32-, 64- and 128-row chunks (the next size up costs 5-30% more below each line, the
 //     previous one 5-50% above it);
 //   * past 100 rows the LDS tiles take over (at 128 rows they are 0-25% faster, at 64 rows 0-60% slower), except
-//     where their grid would leave half the CUs or more idle: the chunks are 10-60% faster there up to 200 rows.
+//     where their grid would leave half the CUs or more idle: the chunks are 10-60% faster there up to 200 rows. With
+//     more than 16 groups FWD_GU goes to the tiles from 32 rows: at 45 to 90 rows of each expert the two are equal
+//     there (32 and 64 experts: within 5%), and Zipf-skewed rows, whose largest groups take many chunks, are 5-30%
+//     faster on the tiles (64 experts, T = 682: 166 us and 220).
 // FWD_DOWN at 25 rows and more takes 128 columns per workgroup as long as that leaves one workgroup per CU (at 64 rows
 // 16% faster with d = 4096, 14% slower with d = 1024 and 16 experts). A grid of few workgroups is bound by the round
 // trips of each: 64-row chunks in place of 128 below 3/4 of a workgroup per CU (f = 8192, d = 1536, 5 groups, 64 rows:
@@ -464,7 +467,7 @@ StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid) {
   const int cols = kind == FWD_GU ? d.d_ff : d.d_model, cus = device_cus();
   const long split_wgs = chunk_bound(d, 16) * (cols / (kind == FWD_GU ? ST_COLS / 2 : ST_COLS));
   if (rows <= 8 && split_wgs <= 5L * cus) return split;
-  if (rows > (tile_grid <= cus / 2 ? 200 : 100)) return none;
+  if (rows > (tile_grid <= cus / 2 ? 200 : kind == FWD_GU && G > 16 ? 32 : 100)) return none;
   int mt = rows <= 24 ? 2 : rows <= 50 ? 4 : 8;
   if (kind == FWD_GU) return StreamPick{mt, 2, mt == 8 ? 2 : 4};
   const auto wgs = [&](int m, int nf) { return chunk_bound(d, 16 * m) * (cols / (64 * nf)); };
