@@ -5,6 +5,7 @@
 // wavefront level: k rounds of a 64-lane maximum over order-preserving keys, ties to the lowest expert index.
 #include "pcmoe_internal.h"
 #include <math.h>
+#include <algorithm>
 
 namespace pcmoe {
 
@@ -376,7 +377,8 @@ struct alignas(JJ * sizeof(T) < 16 ? JJ * sizeof(T) : 16) XRow {  // tensors are
 
 // JJ columns per lane: 4 for up to 16 experts (narrower workgroups, so that 256 of them need only 64 token
 // chunks of partial sums: measured 9 us against 12 us for 8 columns and 128 chunks at T=4096, d=1024), 8 up to 32.
-constexpr int dw_cols_per_lane(int net) { return net == 1 ? 4 : 8; }
+// For more experts, fewer while the accumulators (JJ x NET tiles) fit.
+constexpr int dw_cols_per_lane(int net) { return net == 1 ? 4 : net <= 2 ? 8 : 16 / net; }
 
 template <typename T, int NET, int JJ>
 __global__ __launch_bounds__(256) void route_dw_partial_kernel(int Tn, int d, int E, int tok_per_chunk,
@@ -433,7 +435,7 @@ __global__ __launch_bounds__(256) void route_dw_partial_kernel(int Tn, int d, in
     }
 }
 
-// The same partial sums for more than 32 experts. A wavefront holds 64 experts x 16 chunks of columns and steps through
+// The same partial sums for more than 32 experts and many tokens. A wavefront holds 64 experts x 16 chunks of columns and steps through
 // its tokens 4 at a time with one 16-byte load of dl (lane (q, i): token t + q, experts 4 i .. 4 i + 3, one per MFMA
 // row) and one of x (its chunk of token t + q) per 4 N MFMAs (N columns in a chunk), 16 tokens ahead of the MFMAs.
 // Bound by the fp32 MFMAs. T = 8192, d = 2048, E = 256: 85 us (56 us of MFMA at the peak rate), 184 with one column and
@@ -554,33 +556,38 @@ __global__ __launch_bounds__(256) void route_dw_reduce_kernel(int n4, int nchunk
 // Column blocks of a wavefront's 16 chunks (route_dw_wide_kernel).
 static int dw_wide_cols(const moe_desc& d) { return (int)(d.d_model * elem_bytes(d) / 256); }
 
-// Token chunks of the weight-gradient contraction, a multiple of 32 tokens each: about 256 workgroups for up to 16
-// experts and 1024 up to 32 (4 wavefronts x 16 x JJ columns each), 1024 wavefronts for
-// more (one per SIMD; 2048 and 4096 take as long or longer here and twice and four times as long in the sum).
-static void route_bwd_chunks(const moe_desc& d, int* nch, int* tpc) {
+static int dw_net(int E) { return E <= 16 ? 1 : E <= 32 ? 2 : E <= 64 ? 4 : E <= 128 ? 8 : 16; }
+
+// Token chunks of the weight-gradient contraction, a multiple of 32 tokens each. More than 32 experts take the wide
+// kernel in 1024 wavefronts (one per SIMD; 2048 and 4096 take as long or longer here and twice and four times as long in
+// the sum) where that leaves chunks of 64 tokens or more: in shorter ones its long loop body runs once, from cold
+// instruction caches (T = 4,153, d = 768, E = 64: 18 us, 13 narrow). The narrow kernel takes about 256 workgroups for up to
+// 16 experts and 1024 above (4 wavefronts x 16 x JJ columns each).
+static void route_bwd_chunks(const moe_desc& d, int* nch, int* tpc, bool* wide) {
   const int E = d.n_experts;
-  int units, target;
+  const auto split = [&](int target, int units) {
+    const int maxch = (d.T + 31) / 32;
+    const int want = (target + units - 1) / units;
+    const int n = std::max(std::min(want, maxch), 1);
+    const int per = ((d.T + n - 1) / n + 31) / 32 * 32;
+    *tpc = per;
+    *nch = (d.T + per - 1) / per;
+  };
+  *wide = false;
   if (E > 32) {
-    units = dw_wide_cols(d) * ((E + 63) / 64);
-    target = 1024;
-  } else {
-    const int wg_cols = 64 * dw_cols_per_lane(E <= 16 ? 1 : 2);
-    units = (d.d_model + wg_cols - 1) / wg_cols;
-    target = E <= 16 ? 256 : 1024;
+    split(1024, dw_wide_cols(d) * ((E + 63) / 64));
+    *wide = *tpc >= 64;
   }
-  const int maxch = (d.T + 31) / 32;
-  const int want = (target + units - 1) / units;
-  int n = want < maxch ? want : maxch;
-  if (n < 1) n = 1;
-  int per = (d.T + n - 1) / n;
-  per = ((per + 31) / 32) * 32;
-  *tpc = per;
-  *nch = (d.T + per - 1) / per;
+  if (!*wide) {
+    const int wg_cols = 64 * dw_cols_per_lane(dw_net(E));
+    split(E <= 16 ? 256 : 1024, (d.d_model + wg_cols - 1) / wg_cols);
+  }
 }
 
 size_t route_bwd_ws_bytes(const moe_desc& d) {
   int nch, tpc;
-  route_bwd_chunks(d, &nch, &tpc);
+  bool wide;
+  route_bwd_chunks(d, &nch, &tpc, &wide);
   return align256((size_t)nch * d.n_experts * d.d_model * sizeof(float));
 }
 
@@ -597,11 +604,13 @@ static hipError_t route_bwd_t(const moe_desc& d, const void* x, const float* log
                        logits, idx, w, dgate, dl);
   }
   int nch, tpc;
-  route_bwd_chunks(d, &nch, &tpc);
-  float* part = (float*)ws;
+  bool wide;
+  route_bwd_chunks(d, &nch, &tpc, &wide);
+  // one chunk (up to 32 tokens): its sums are the result, without the sum over chunks and its launch (6 us)
+  float* part = nch == 1 ? dwr : (float*)ws;
   {
     KernelTimer kt("route_dw_partial", s);
-    if (E > 32) {
+    if (wide) {
       const int cb = dw_wide_cols(d);
       const dim3 grid((cb * ((E + 63) / 64) + 3) / 4, nch);
       if (E % 4 == 0)
@@ -611,17 +620,20 @@ static hipError_t route_bwd_t(const moe_desc& d, const void* x, const float* log
         hipLaunchKernelGGL((route_dw_wide_kernel<T, false>), grid, dim3(256), 0, s, d.T, d.d_model, E, tpc, cb,
                            (const T*)x, dl, part);
     } else {
-      const int wg_cols = 64 * dw_cols_per_lane(E <= 16 ? 1 : 2);
+      const int wg_cols = 64 * dw_cols_per_lane(dw_net(E));
       const dim3 grid((d.d_model + wg_cols - 1) / wg_cols, nch);
 #define RB_LAUNCH(NET)                                                                                       \
   hipLaunchKernelGGL((route_dw_partial_kernel<T, NET, dw_cols_per_lane(NET)>), grid, dim3(256), 0, s, d.T, \
                      d.d_model, E, tpc, (const T*)x, dl, part)
       if (E <= 16) RB_LAUNCH(1);
-      else RB_LAUNCH(2);
+      else if (E <= 32) RB_LAUNCH(2);
+      else if (E <= 64) RB_LAUNCH(4);
+      else if (E <= 128) RB_LAUNCH(8);
+      else RB_LAUNCH(16);
 #undef RB_LAUNCH
     }
   }
-  {
+  if (nch > 1) {
     KernelTimer kt("route_dw_reduce", s);
     const int n4 = E * d.d_model / 4;
     const int blocks = (n4 + 256 / RED_G - 1) / (256 / RED_G);

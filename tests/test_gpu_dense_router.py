@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 CASES = [  # T, d, E, k, shared, dtype
     (1, 128, 9, 2, 0, "bf16"), (15, 256, 16, 3, 1, "bf16"), (17, 128, 33, 8, 2, "f32"), (33, 384, 50, 5, 3, "bf16"),
-    (64, 128, 64, 1, 0, "f32"), (129, 640, 65, 4, 0, "bf16"), (1030, 256, 256, 8, 0, "bf16"),
+    (64, 128, 64, 1, 0, "f32"), (129, 640, 65, 4, 0, "bf16"), (1030, 256, 256, 8, 0, "bf16"), (16500, 256, 64, 2, 0, "bf16"),
+    (8300, 256, 130, 4, 0, "f32"), (33000, 128, 33, 1, 0, "bf16"),
     (515, 128, 255, 6, 1, "f32"),
 ]
 
