@@ -435,11 +435,11 @@ __global__ __launch_bounds__(256) void route_dw_partial_kernel(int Tn, int d, in
     }
 }
 
-// The same partial sums for more than 32 experts and many tokens. A wavefront holds 64 experts x 16 chunks of columns and steps through
-// its tokens 4 at a time with one 16-byte load of dl (lane (q, i): token t + q, experts 4 i .. 4 i + 3, one per MFMA
-// row) and one of x (its chunk of token t + q) per 4 N MFMAs (N columns in a chunk), 16 tokens ahead of the MFMAs.
-// Bound by the fp32 MFMAs. T = 8192, d = 2048, E = 256: 85 us (56 us of MFMA at the peak rate), 184 with one column and
-// one 4-byte load of dl per MFMA; T = 16384, E = 64: 47 us, 81 before.
+// The same partial sums for more than 32 experts and many tokens. A wavefront holds 64 experts x 16 groups of N columns
+// (16 bytes of x) and steps through its tokens 4 at a time with one 16-byte load of dl (lane (q, i): token t + q, experts
+// 4 i .. 4 i + 3, one per MFMA row) and one of x (its columns of token t + q) per 4 N MFMAs, 16 tokens ahead of the MFMAs.
+// Bound by the fp32 MFMAs. Bit for bit the sums of the narrow kernel. Both launches, narrow and wide: T = 8192, d = 2048,
+// E = 256 181 and 96 us (56 us of MFMA at the peak rate); T = 16384, E = 64 78 and 62.
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256, 2) void route_dw_wide_kernel(int Tn, int d, int E, int tok_per_chunk, int col_blocks,
                                                                const T* __restrict__ x, const float* __restrict__ dl,
@@ -558,30 +558,24 @@ static int dw_wide_cols(const moe_desc& d) { return (int)(d.d_model * elem_bytes
 
 static int dw_net(int E) { return E <= 16 ? 1 : E <= 32 ? 2 : E <= 64 ? 4 : E <= 128 ? 8 : 16; }
 
-// Token chunks of the weight-gradient contraction, a multiple of 32 tokens each. More than 32 experts take the wide
-// kernel in 1024 wavefronts (one per SIMD; 2048 and 4096 take as long or longer here and twice and four times as long in
-// the sum) where that leaves chunks of 64 tokens or more: in shorter ones its long loop body runs once, from cold
-// instruction caches (T = 4,153, d = 768, E = 64: 18 us, 13 narrow). The narrow kernel takes about 256 workgroups for up to
-// 16 experts and 1024 above (4 wavefronts x 16 x JJ columns each).
+// Token chunks of the weight-gradient contraction, a multiple of 32 tokens each: as many as give the narrow kernel about
+// 256 workgroups for up to 16 experts and 1024 above (4 wavefronts x 16 x JJ columns each). The chunk is the length of an
+// fp32 accumulator and so sets the error of dW_router (T = 8192, d = 2048, E = 256: 3.0e-7 of its norm over 256 tokens,
+// 4.1e-7 over 512): the wide kernel takes the same chunks, though it would fill the chip with fewer. With 33 to 64 experts
+// it is left to chunks of 64 tokens and more: in shorter ones its long loop body runs once, from cold instruction caches
+// (partial sums and their sum, narrow and wide, 32-token chunks: E = 64, T = 300, d = 2048 16.3 and 18.7 us, T = 4,153,
+// d = 768 25.5 and 27.9; E = 128, T = 2,048, d = 2048 40.6 and 38.4, E = 256, T = 4,096, d = 512 47.4 and 38.7).
 static void route_bwd_chunks(const moe_desc& d, int* nch, int* tpc, bool* wide) {
   const int E = d.n_experts;
-  const auto split = [&](int target, int units) {
-    const int maxch = (d.T + 31) / 32;
-    const int want = (target + units - 1) / units;
-    const int n = std::max(std::min(want, maxch), 1);
-    const int per = ((d.T + n - 1) / n + 31) / 32 * 32;
-    *tpc = per;
-    *nch = (d.T + per - 1) / per;
-  };
-  *wide = false;
-  if (E > 32) {
-    split(1024, dw_wide_cols(d) * ((E + 63) / 64));
-    *wide = *tpc >= 64;
-  }
-  if (!*wide) {
-    const int wg_cols = 64 * dw_cols_per_lane(dw_net(E));
-    split(E <= 16 ? 256 : 1024, (d.d_model + wg_cols - 1) / wg_cols);
-  }
+  const int wg_cols = 64 * dw_cols_per_lane(dw_net(E));
+  const int ncol = (d.d_model + wg_cols - 1) / wg_cols;
+  const int maxch = (d.T + 31) / 32;
+  const int want = ((E <= 16 ? 256 : 1024) + ncol - 1) / ncol;
+  const int n = std::max(std::min(want, maxch), 1);
+  const int per = ((d.T + n - 1) / n + 31) / 32 * 32;
+  *tpc = per;
+  *nch = (d.T + per - 1) / per;
+  *wide = E > 64 || (E > 32 && per >= 64);
 }
 
 size_t route_bwd_ws_bytes(const moe_desc& d) {

@@ -50,6 +50,17 @@ def test_workspace_sizes():
     assert P.moe_workspace_size(desc(top_k=9), P.MOE_WS_PERMUTE) == 0   # invalid descriptor
 
 
+@pytest.mark.parametrize("T,d,E,tokens", [(8192, 2048, 256, 256), (8192, 4096, 128, 256), (16384, 2048, 64, 128),
+                                          (8192, 2048, 64, 64), (16384, 512, 96, 64)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_router_gradient_accumulator_length(T, d, E, tokens, dtype):
+    """The workspace of moe_route_bwd holds one [E, d] fp32 partial sum per chunk of tokens, and a chunk is the length
+    of an fp32 accumulator: whatever kernel computes it, it is no longer than the narrow kernel's grid asks for (1,024
+    workgroups of 4 x 16 x 16 / tiles columns; tiles = experts / 16, rounded up to a power of two)."""
+    nbytes = P.moe_workspace_size(desc(T=T, d_model=d, d_ff=128, n_experts=E, dtype=dtype), P.MOE_WS_ROUTE_BWD)
+    assert nbytes >= (T // tokens) * E * d * 4
+
+
 FAKE = 0x1000  # never dereferenced: every call below fails validation first
 
 

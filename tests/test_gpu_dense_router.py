@@ -78,3 +78,28 @@ def test_zero_gradient_skips_infinite_weights(dtype):
     tol = 2 ** -8 if dtype == "bf16" else 1e-5
     assert (dx.cpu().double() - ref).abs().max() <= tol * ref.abs().max()
     assert np.isfinite(dx.float().cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("T,d,E,tokens", [(8192, 2048, 256, 256), (16384, 2048, 64, 128), (8192, 2048, 64, 64)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_router_gradient_error(T, d, E, tokens, dtype):
+    """The error of dW_router's fp32 sums against fp64 of the same gradients is that of accumulators over `tokens` tokens.
+    A sum of n independent terms, rounded after each, is off by u c sqrt(n / 2) of its size: the j-th partial sum is
+    sqrt(j / n) of it, and a rounding is off by c = 0.425 units u = 2^-24 of the value in the mean (mantissas spread
+    over their logarithm). The chunks are then added 16 ways and the 16 sums in turn. 10% are left for the spread."""
+    log(f"[dW_router error] T={T} d={d} E={E} {dtype}")
+    k = 2
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    n = lambda *s: torch.randn(*s, device="cuda", generator=gen)
+    x, logits, dgate = n(T, d).to(torch.bfloat16 if dtype == "bf16" else torch.float32), n(T, E), n(T, k)
+    topk_w, idx = torch.topk(torch.softmax(logits, 1), k)
+    desc = P.make_desc(T, d, 128, E, k, 0, E, 0, False, dtype)
+    dl, dwr = torch.empty(T, E, device="cuda"), torch.empty(E, d, device="cuda")
+    ws = torch.empty(max(P.moe_workspace_size(desc, P.MOE_WS_ROUTE_BWD), 1), dtype=torch.uint8, device="cuda")
+    P.moe_route_bwd(desc, x, logits, idx.int().contiguous(), topk_w.contiguous(), dgate, dl, dwr, ws, ws.numel())
+    ref = dl.double().t().contiguous() @ x.double()
+    err = float((dwr.double() - ref).norm() / ref.norm())
+    steps = tokens + T / tokens / 16 + 16
+    bound = 1.1 * 2 ** -24 * 0.425 * (steps / 2) ** 0.5
+    log(f"[dW_router error] {err:.3e}, bound {bound:.3e}")
+    assert err <= bound
