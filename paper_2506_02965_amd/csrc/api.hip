@@ -282,7 +282,9 @@ moe_status moe_permute_bwd(const moe_desc* d, const void* dx_perm, const int32_t
   moe_status st = check_desc(d);
   if (st) return st;
   NEED(dx_perm); NEED(slot_to_row); NEED(dx);
-  if (dlogits) NEED(w_router);
+  if (dlogits) {  // read in 16-byte vectors like every other tensor
+    NEED(dlogits); NEED(w_router);
+  }
   return hip_status(launch_permute_bwd(*d, dx_perm, slot_to_row, dlogits, w_router, dx, stream), "moe_permute_bwd");
 }
 

@@ -138,6 +138,16 @@ def test_null_pointers_and_workspace():
     assert ei.value.status == P.MOE_ERR_INVALID_ARGUMENT
 
 
+@pytest.mark.parametrize("renorm", [False, True])
+def test_permute_bwd_checks_its_router_operands(renorm):
+    """dlogits and w_router of the hand-back are 16-byte aligned like every other tensor, or the call is refused."""
+    d = desc(n_experts=16, renormalize=renorm)
+    for dlogits, w_router, what in ((FAKE + 4, FAKE, "dlogits"), (FAKE, FAKE + 8, "w_router"), (FAKE, None, "w_router")):
+        with pytest.raises(P.MoeError) as ei:
+            P.moe_permute_bwd(d, FAKE, FAKE, dlogits, w_router, FAKE, stream=0)
+        assert ei.value.status == P.MOE_ERR_INVALID_ARGUMENT and what in P.last_error()
+
+
 @pytest.mark.parametrize("kw,ptrs,status", [
     (dict(lr=0.0), {}, P.MOE_ERR_INVALID_ARGUMENT),
     (dict(lr=float("nan")), {}, P.MOE_ERR_INVALID_ARGUMENT),
