@@ -441,19 +441,37 @@ static hipError_t run_rows(const moe_desc& d, const GemmArgs& a, const PlanArgs&
   return hipGetLastError();
 }
 
-// Which streaming kernel a contraction takes, by the expected rows per group (every expert equally likely) and the
-// workgroups its grid has. Each line was drawn from timings of all the variants and of the LDS tiles over eight layer
-// shapes (d 256 to 4096, f 512 to 14336, 4 to 128 experts, with and without shared experts, uniform and Zipf-skewed)
-// at 1 to 256 rows per group:
+// Rows per group: `mean` where every expert is equally likely, `most` where every slot goes to a hosted expert (a shard
+// cannot know how hot its experts are; a full layer's two are equal).
+struct GroupRows {
+  double mean, most;
+};
+static GroupRows group_rows(const moe_desc& d) {
+  const double slots = (double)d.T * d.top_k, shared = (double)d.T * d.n_shared, G = d.local_count + d.n_shared;
+  return {(slots * d.local_count / d.n_experts + shared) / G, (slots + shared) / G};
+}
+
+// Which streaming kernel a contraction takes, by the rows per group and the workgroups its grid has. The counts stay on
+// the device, so a line has to hold however the rows are spread: a group of many rows reads its weights once per chunk,
+// where the LDS tiles read them once per 256 rows. Each line was drawn from timings of all the variants and of the LDS
+// tiles over 40 layers (d 256 to 4096, f 512 to 14336, 3 to 128 groups, with and without shared experts, whole layers
+// and shards) at 1 to 200 rows per group, spread uniformly, Zipf-skewed (exponent 1.1) and with one expert in every
+// token; no call was more than 2% slower than on the tiles. Times are tiles -> streamed, us, uniform and skewed rows:
 //   * up to 8 rows, at most 5 workgroups per CU: the split over K (2-20% under the 32-row kernel, which is 5-20%
 //     under it beyond 5 per CU);
 //   * up to 24, 50 and 100 rows: 32-, 64- and 128-row chunks (the next size up costs 5-30% more below each line, the
-//     previous one 5-50% above it);
-//   * past 100 rows the LDS tiles take over (at 128 rows they are 0-25% faster, at 64 rows 0-60% slower), except
-//     where their grid would leave half the CUs or more idle: the chunks are 10-60% faster there up to 200 rows. With
-//     more than 16 groups FWD_GU goes to the tiles from 32 rows: at 45 to 90 rows of each expert the two are equal
-//     there (32 and 64 experts: within 5%), and Zipf-skewed rows, whose largest groups take many chunks, are 5-30%
-//     faster on the tiles (64 experts, T = 682: 166 us and 220).
+//     previous one 5-50% above it). A shard takes the size for twice its even share;
+//   * where the tiles would leave half the CUs or more idle, chunks up to 200 rows: 10-60% faster, skewed or not;
+//   * else the down projection goes to the tiles past 50 rows (d = 2048, f = 1408, 16 groups, 64 rows: 34 -> 25, 35 ->
+//     40; d = 4096, f = 2816, 8 groups: 64 -> 44, 64 -> 78);
+//   * gate/up, which also saves the launch of the tile plan (6 us) when streamed: where the tiles take one round of the
+//     chip, past 80 rows (d = 2048, f = 1408, 16 groups, 99 rows: 54 -> 63, 61 -> 75); up to two rounds, past 100 rows
+//     with d_model up to 1536 (d = 1024, f = 2816, 16 groups, 99 rows: 58 -> 52, 56 -> 63), 50 above (d = 2048, 79 rows:
+//     103 -> 93, 98 -> 110); a shard, past 64 slots of its tokens per hosted expert (16 of 64 experts, top-4, T = 320:
+//     41 -> 41, 57 -> 86);
+//   * both go to the tiles past 32 rows with more than 16 groups (down, 64 experts, 39 rows: 109 -> 89, 91 -> 96) or
+//     where the tiles take more than two rounds (gate/up, d = 2048, f = 5632, 16 groups, 50 rows: 159 -> 159, 149 ->
+//     178), there also past 1,024 tokens (gate/up, 64 experts, top-1, T = 1280: 149 -> 145, all to one expert 51 -> 69).
 // FWD_DOWN at 25 rows and more takes 128 columns per workgroup as long as that leaves one workgroup per CU (at 64 rows
 // 16% faster with d = 4096, 14% slower with d = 1024 and 16 experts). A grid of few workgroups is bound by the round
 // trips of each: 64-row chunks in place of 128 below 3/4 of a workgroup per CU (f = 8192, d = 1536, 5 groups, 64 rows:
@@ -463,11 +481,23 @@ StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid) {
   const StreamPick none{0, 0, 0}, split{1, 1, 2};
   if (d.dtype != MOE_BF16) return none;
   const int G = d.local_count + d.n_shared;
-  const double rows = ((double)d.T * d.top_k * d.local_count / d.n_experts + (double)d.T * d.n_shared) / G;
+  const GroupRows gr = group_rows(d);
+  const double rows = std::min(2 * gr.mean, gr.most);
   const int cols = kind == FWD_GU ? d.d_ff : d.d_model, cus = device_cus();
   const long split_wgs = chunk_bound(d, 16) * (cols / (kind == FWD_GU ? ST_COLS / 2 : ST_COLS));
   if (rows <= 8 && split_wgs <= 5L * cus) return split;
-  if (rows > (tile_grid <= cus / 2 ? 200 : kind == FWD_GU && G > 16 ? 32 : 100)) return none;
+  if (tile_grid <= cus / 2) {
+    if (gr.mean > 200) return none;
+  } else {
+    int limit = 50;
+    if (kind == FWD_GU) {
+      limit = tile_grid <= cus ? 80 : d.d_model <= 1536 ? 100 : 50;
+      if (d.local_count < d.n_experts) limit = std::min(limit, 64);
+    }
+    const bool rounds = tile_grid > 2L * cus;  // the tiles fill more than two rounds
+    if (G > 16 || rounds) limit = 32;
+    if (gr.most > limit || (rounds && d.T > 1024)) return none;
+  }
   int mt = rows <= 24 ? 2 : rows <= 50 ? 4 : 8;
   if (kind == FWD_GU) return StreamPick{mt, 2, mt == 8 ? 2 : 4};
   const auto wgs = [&](int m, int nf) { return chunk_bound(d, 16 * m) * (cols / (64 * nf)); };

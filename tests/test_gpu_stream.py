@@ -3,7 +3,10 @@
 more groups. The backward reads the tile plan that the gate/up launch wrote."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2506_02965_amd import pcmoe as P
+from paper_2506_02965_amd.layer import LayerWeights, MoELayer
 from paper_2506_02965_amd.synth import LayerConfig, make_inputs
 from gpu_util import check_full, log, run_gpu
 
@@ -83,3 +86,34 @@ def test_stream_shard_one_token():
         inp = make_inputs(cfg, with_dy=True)
         layer, _ = run_gpu(cfg, inp)
         check_full(cfg, inp, layer)
+
+
+def launches(T, d, f, E, k, local=None, S=0, backward=False):
+    """Names of the launches of a layer's expert passes."""
+    cfg = LayerConfig("rt", T=T, d=d, f=f, E=E, k=k, local_count=local, n_shared=S, router_backward=False,
+                      backward=backward)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    new = lambda *s: torch.randn(*s, device="cuda", dtype=torch.bfloat16, generator=gen) * 0.02
+    G = cfg.n_groups
+    w = LayerWeights(new(T, d), new(E, d), None, 1, new(G, f, d), new(G, f, d), new(G, d, f), new(T, d))
+    layer = MoELayer(cfg)
+    P.moe_kernel_timing(True)
+    layer.forward(w)
+    if backward:
+        layer.backward(w)
+    torch.cuda.synchronize()
+    names = set(P.moe_kernel_timing_report())
+    P.moe_kernel_timing(False)
+    return names
+
+
+@pytest.mark.parametrize("T,d,f,E,k,local,tiles", [
+    (777, 1024, 2816, 16, 2, None, False), (792, 2048, 1408, 16, 2, None, True), (640, 2048, 2816, 16, 2, None, True),
+    (400, 2048, 5632, 16, 2, None, True), (200, 2048, 5632, 16, 2, None, False), (1280, 2048, 1408, 64, 1, None, True),
+    (192, 2048, 1408, 64, 4, 16, False), (320, 2048, 1408, 64, 4, 16, True), (384, 1024, 2816, 32, 2, 8, True),
+])
+def test_gate_up_route(T, d, f, E, k, local, tiles):
+    """Gate/up goes to the LDS tiles (which need the tile plan launched first) at row counts where streamed chunks are
+    slower once the routing is skewed, though they are not on uniform rows."""
+    log(f"[stream] route of gate/up, T={T} d={d} f={f} E={E} k={k} local={local}")
+    assert ("ffn_plan" in launches(T, d, f, E, k, local)) == tiles
