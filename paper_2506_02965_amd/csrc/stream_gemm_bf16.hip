@@ -534,17 +534,29 @@ hipError_t stream_down(const moe_desc& d, const StreamPick& k, const GemmArgs& a
 
 // The LDS tiles of dX take about 1.25 us per 64-deep step (the round trip of a K-tile's loads), 2 f / 64 of them in a
 // chain, beside the weight gradient's stores in the same launch; streamed, dX reads its weights at the memory's rate, but
-// before those stores. So it is streamed where the chain is longer than both together: us, paired tiles and dX +
-// dW_gate, dW_up streamed: d = 1536, f = 8192, 5 groups, 16 rows: 320 and 175; d = 1024, f = 2816, 16 groups, 6 rows: 116
-// and 90, 110 rows: 146 and 140; d = 4096, f = 14336, 8 groups: 716 and 856; d = 3072, f = 768, 32 groups: 139 and 141;
-// d = 256, f = 512, 8 groups: 17 and 20. 16-row chunks up to 24 rows, 32 above (32 rows: 112 and 101 with d = 1024).
-// (The same kernel for dG|dU lost to the paired tiles in every one of these.)
+// before those stores. So it is streamed where the chain is longer than both together: up to 50 rows per group where it
+// is less than 1.4 times as long, else up to 128 (and 256 where a shard's experts take every slot); at d_model >= 4096,
+// whose pipelined tiles take a step in less time, only where it is twice as long. us, paired tiles -> dX and
+// dW_gate, dW_up streamed, uniform and Zipf-skewed rows (one expert in every token is between them or gains more):
+//   d = 1536, f = 8192, 5 groups, 14 rows: 318 -> 175, 317 -> 175;
+//   d = 1024, f = 14336, 8 groups, 125 rows: 638 -> 499, 695 -> 492;
+//   d = 1024, f = 2816, 16 groups: 6 rows 108 -> 86, 76 -> 75; 50 rows 124 -> 121, 141 -> 134;
+//     not streamed: 99 rows 139 -> 142, 152 -> 149; 125 rows 147 -> 175, 161 -> 178;
+//   8 of 32 experts, top-4, d = 1024, f = 2816: 20 rows 71 -> 55, 100 -> 73; not streamed: 125 rows 104 -> 91, 136 -> 167;
+//   d = 768, f = 1408, 16 groups, not streamed: 36 rows 42 -> 47, 64 -> 46;
+//   d = 4096, f = 14336, 2 groups, 50 rows: 478 -> 328, 563 -> 352;
+//   d = 4096, f = 2816, 4 groups, not streamed: 24 rows 95 -> 93, 98 -> 106; 128 rows 144 -> 179, 144 -> 176.
+// 16-row chunks up to 24 rows, 32 above (32 rows: 112 and 101 us with d = 1024).
+// (The same kernel for dG|dU lost to the paired tiles wherever it was timed.)
 int stream_dx_pick(const moe_desc& d) {
   const int G = d.local_count + d.n_shared;
-  const double rows = ((double)d.T * d.top_k * d.local_count / d.n_experts + (double)d.T * d.n_shared) / G;
+  const GroupRows gr = group_rows(d);
   const double chain_us = 1.25 * (2.0 * d.d_ff / 64), bytes = 8.0 * d.d_ff * d.d_model * G;
-  if (rows > 128 || chain_us <= 1.2 * bytes / 5.2e6 + 20) return 0;
-  return rows <= 24 ? 1 : 2;
+  const double stream_us = 1.2 * bytes / 5.2e6 + 24;
+  if (chain_us <= stream_us) return 0;
+  if (d.d_model >= 4096 && chain_us < 2 * stream_us) return 0;
+  if (chain_us < 1.4 * stream_us ? gr.most > 50 : gr.mean > 128 || gr.most > 256) return 0;
+  return gr.mean <= 24 ? 1 : 2;
 }
 hipError_t stream_dx(const moe_desc& d, int mt, const GemmArgs& a, hipStream_t s, const char* name) {
   const int n_blocks = d.d_model / DX_COLS;

@@ -48,11 +48,12 @@ CASES = {
 }
 
 
-# a long d_ff beside few columns: the streamed dX, 16- and 32-row chunks
+# a long d_ff beside few columns: the streamed dX, 16- and 32-row chunks, several groups of more than one chunk
 CASES.update({
     "dx16": _case(24, 256, 2816, 4, [0, 16, 17], 87),
     "dx32": _case(65, 128, 2944, 4, [65, 33, 0], 88, n_shared=1),
     "dx_mid": _case(150, 384, 2816, 6, [31, 32, 0, 129], 89),
+    "dx_skew": _case(150, 256, 2816, 6, [100, 70, 33, 31, 0], 90),
 })
 
 
@@ -117,3 +118,43 @@ def test_gate_up_route(T, d, f, E, k, local, tiles):
     slower once the routing is skewed, though they are not on uniform rows."""
     log(f"[stream] route of gate/up, T={T} d={d} f={f} E={E} k={k} local={local}")
     assert ("ffn_plan" in launches(T, d, f, E, k, local)) == tiles
+
+
+@pytest.mark.parametrize("T,d,f,E,k,local,streamed", [
+    (400, 1024, 2816, 16, 2, None, True), (1024, 1024, 2816, 16, 2, None, False), (48, 4096, 2816, 4, 2, None, False),
+    (60, 4096, 5632, 2, 1, None, True), (288, 768, 1408, 16, 2, None, False), (500, 1024, 2816, 32, 4, 8, True),
+    (1000, 1024, 2816, 32, 4, 8, False),
+])
+def test_dx_route(T, d, f, E, k, local, streamed):
+    """dX is streamed only where that beats the launch it otherwise shares with dW_gate, dW_up."""
+    log(f"[stream] route of dX, T={T} d={d} f={f} E={E} k={k} local={local}")
+    names = launches(T, d, f, E, k, local, backward=True)
+    assert ("gemm_bwd_dx" in names) == streamed and ("gemm_bwd_dx+wgrad_gate_up" in names) != streamed
+
+
+def _no_tokens(inp):
+    inp.logit_bias[0, 0] = -1e4
+
+
+@pytest.mark.parametrize("name", ["shard_one_group", "shard_without_rows", "two_groups"])
+def test_streamed_dx_beside_pipelined_weight_gradient(name):
+    """d_model = 4096: dX streamed, and dW_gate, dW_up in a launch of their own on the pipelined tile, over one chunk of
+    rows, several, and none."""
+    kw = dict(d=4096, E=2, k=1)
+    cfg, edit = {
+        "shard_one_group": (LayerConfig("dp1", T=130, f=2048, local_count=1, router_backward=False, seed=91, **kw), None),
+        "shard_without_rows": (LayerConfig("dp2", T=60, f=2048, local_count=1, router_backward=False, bias="forced_empty",
+                                           seed=92, **kw), _no_tokens),
+        "two_groups": (LayerConfig("dp3", T=44, f=5632, seed=93, **kw), None),
+    }[name]
+    log(f"[stream] dX at d_model 4096: {name}")
+    inp = make_inputs(cfg, with_dy=True)
+    if edit:
+        edit(inp)
+    P.moe_kernel_timing(True)
+    layer, _ = run_gpu(cfg, inp)
+    names = set(P.moe_kernel_timing_report())
+    P.moe_kernel_timing(False)
+    assert {"gemm_bwd_dx", "gemm_wgrad_gate_up"} <= names
+    errs = check_full(cfg, inp, layer)
+    log(f"[stream] {name}: " + " ".join(f"{k}={v:.2e}" for k, v in errs.items()))
