@@ -92,7 +92,10 @@ size_t moe_workspace_size(const moe_desc* desc, int which);
  * Gating, Alg. 7: scores s = W_g h (+ bias), p = softmax(s), I = TopKIndices(p), w = p[I]
  * (renormalised over I when desc->renormalize). Selection is decided on the fp32 scores,
  * which are formed with fp64 accumulation and rounded once; equal scores rank the lower
- * expert index first; slots j are in descending score order.
+ * expert index first; slots j are in descending score order. The order of the fp64 sums follows T and the device's
+ * number of compute units: calls with equal inputs and T give equal bits on one device; the same token in a batch of
+ * another size, or on a device with another number of units, can differ in the last bit of a score (and in a
+ * selection that hangs on it) where fp64 does not hold the sum exactly.
  *   x          [T, d]   dtype
  *   w_router   [E, d]   dtype
  *   logit_bias [bias_groups, E] fp32 or NULL; token t adds row t / (T / bias_groups)

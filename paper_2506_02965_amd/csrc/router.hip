@@ -1,8 +1,10 @@
 // Gating (Alg. 7: scores, softmax, TopKIndices, w = p[I]) and its adjoint on the data owner.
 //
-// Scores are accumulated in fp64 (MFMA or FMA) from the exact products of the stored inputs and rounded
-// once to fp32, so the top-k decision is reproducible from the inputs alone. Selection happens at
-// wavefront level: k rounds of a 64-lane maximum over order-preserving keys, ties to the lowest expert index.
+// Scores are accumulated in fp64 (MFMA or FMA) from the products of the stored inputs (exact in fp64) and rounded once to
+// fp32. The order of a score's sum follows the tiling, which goes by the batch size and the device's CU count: equal
+// calls give equal bits, and where fp64 holds the sum exactly (bf16 inputs, as long as no product is smaller than about
+// 2^-37 of the sum) so do other batches; else a score can differ in its last fp32 bit, in about one of 10^8, and a
+// selection that hangs on that bit with it. Selection happens at wavefront level: k rounds of a 64-lane maximum over order-preserving keys, ties to the lowest expert index.
 #include "pcmoe_internal.h"
 #include <math.h>
 #include <algorithm>

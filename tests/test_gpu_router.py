@@ -1,7 +1,6 @@
 """The router forward at the edges of its dispatch (1, 4, 16 or 32 tokens per workgroup, 16 to 256 expert columns)
 against fp64 scores: selection bit-exact, scores within one ulp of fp32, gate weights within 1e-5 (the bar of the
 parity tests)."""
-import numpy as np
 import pytest
 import torch
 
@@ -79,3 +78,31 @@ def test_route_special_scores(T):
     s, logits, idx, gw = route(T, d, E, 4, "bf16", bias=bias)
     assert torch.equal(idx, torch.tensor([64, 69, 0, 1], dtype=torch.int32).expand(T, 4))
     assert torch.equal(gw, torch.tensor([1.0, 0.0, 0.0, 0.0]).expand(T, 4))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_route_batch_size(dtype):
+    """The same tokens in batches of different size (1, 4, 16 and 32 tokens per workgroup). Where fp64 holds every sum
+    exactly (inputs on a grid: here multiples of 2^-6 of at most 8 significant bits) the scores are the same bits in
+    each; else they lie within one ulp of fp32, and calls of the same size give the same bits."""
+    d, E, k, sizes = 640, 64, 6, (1, 300, 2000, 5000)
+    log(f"[router] batch size {dtype}")
+    gen = torch.Generator().manual_seed(8)
+    all_x, all_w = torch.randn(max(sizes), d, generator=gen), torch.randn(E, d, generator=gen) * d ** -0.5
+    grid = lambda t: (t * 64).round().clamp(-127, 127) / 64
+
+    def run(T, on_grid):
+        def same_tokens(x, w):
+            x.copy_(grid(all_x[:T]) if on_grid else all_x[:T])
+            w.copy_(grid(all_w) if on_grid else all_w)
+        return route(T, d, E, k, dtype, edit=same_tokens)
+
+    s, logits, idx, gw = run(max(sizes), True)
+    assert torch.equal(logits, s.float())   # the exact sums, rounded once
+    for T in sizes[:-1]:
+        _, lg, ix, g = run(T, True)
+        assert torch.equal(lg, logits[:T]) and torch.equal(ix, idx[:T]) and torch.equal(g, gw[:T]), T
+    for T in sizes:
+        s, lg, ix, g = run(T, False)
+        check_logits(lg, s.float().numpy())
+        assert all(torch.equal(a, b) for a, b in zip((lg, ix, g), run(T, False)[1:])), T
