@@ -83,9 +83,10 @@ def small_cases():
     C["tail_tiles_forced_counts"] = (LayerConfig("tt", T=2048, d=256, f=2048, E=len(tail_counts), k=2, bias="party",
                                                  parties=2048, seed=26), forced_counts)
 
-    # d_model = 4096 selects the software-pipelined one-wavefront-per-SIMD tile for every contraction but the down
-    # projection: ragged tail m-tiles (about 150 rows per expert, 600 shared-expert rows), a last n-tile of 128
-    # columns (f = 384), weight gradients with an odd number of 32-deep K-tiles, and groups with no rows at all
+    # d_model = 4096 selects the software-pipelined one-wavefront-per-SIMD tile for the backward's contractions (gate/up,
+    # which takes it with more rows, is streamed here; the forced runs below put it on the tile): ragged tail m-tiles
+    # (about 150 rows per expert, 600 shared-expert rows), a last n-tile of 128 columns (f = 384), weight gradients with
+    # an odd number of 32-deep K-tiles, and groups with no rows at all
     C["pipelined_d4096_ragged_shared"] = (LayerConfig("p4", T=600, d=4096, f=384, E=8, k=2, n_shared=1, seed=32), None)
 
     def two_empty(inp):
@@ -184,6 +185,20 @@ def test_layer_small_ticket_tiles_forced():
     """The bf16 small cases with the default tiles and ticket-claimed weight-gradient tiles in every paired launch,
     down to groups with a single tile."""
     run_small_in_child("ticket tiles forced", PCMOE_DYN="2")
+
+
+@pytest.mark.timeout(400)
+def test_layer_small_forward_tiles_forced():
+    """The bf16 small cases with the forward's contractions on the default LDS tiles, which few rows per expert leave to
+    the streamed kernels: each tile on the workgroup that its index implies."""
+    run_small_in_child("forward tiles forced", PCMOE_GEMM_TILES="0=256x256w16,1=256x256w16")
+
+
+@pytest.mark.timeout(400)
+def test_layer_small_pipelined_tile_static():
+    """The bf16 small cases with the pipelined tile on all six contractions and no tile claimed at run time (but in the
+    launches that fill 8 rounds of the chip)."""
+    run_small_in_child("pipelined tile, static", PCMOE_GEMM_TILES=",".join(f"{k}=256x256w4" for k in range(6)))
 
 
 def test_deterministic_bits():

@@ -45,6 +45,11 @@ CASES = {
     "rows128": _case(515, 384, 256, 8, [0, 127, 128, 129, 257, 1], 78),
     "rows128_narrow": _case(400, 1024, 128, 12, [0, 127, 128, 129, 1], 86),
     "rows128_wide": _case(1100, 1024, 128, 40, [0, 127, 128, 129, 258], 79),
+    # ... and two column blocks per wavefront of the down projection
+    "rows128_two_blocks": _case(600, 2048, 128, 8, [0, 127, 128, 129, 258, 1], 94),
+    # more than 128 groups: a lane of the group scan counts eight of them
+    "split_130_groups": _case(300, 128, 128, 130, [0, 16, 17, 40, 1], 95),
+    "split_258_groups": _case(64, 128, 256, 256, [0, 17, 33, 1], 96, n_shared=2),
 }
 
 
@@ -87,6 +92,35 @@ def test_stream_shard_one_token():
         inp = make_inputs(cfg, with_dy=True)
         layer, _ = run_gpu(cfg, inp)
         check_full(cfg, inp, layer)
+
+
+@pytest.mark.parametrize("name", ["split", "rows32", "rows64", "rows128", "dx_mid", "dx_skew"])
+def test_non_finite_weights_stay_in_their_rows(name):
+    """A NaN in one expert's W_gate and an infinity in another's W_down reach the rows of these experts alone: every
+    other row, padded ones of the same chunk included, has the bits of a run without them."""
+    cfg, counts = CASES[name]
+    log(f"[stream] non-finite weights: {name}")
+    inp = make_inputs(cfg, with_dy=True)
+    forced(inp, counts)
+    clean, _ = run_gpu(cfg, inp)
+    bad, inf = [e for e, c in enumerate(counts) if c > 1][:2]
+    inp.w_gate[bad, 5] = np.nan
+    inp.w_down[inf, 7] = np.inf
+    layer, _ = run_gpu(cfg, inp)
+    off = np.concatenate([[0], np.cumsum(counts)])
+    rows = lambda e: slice(off[e], off[e + 1])
+    assert torch.equal(layer.offsets, clean.offsets) and torch.equal(layer.slot_to_row, clean.slot_to_row)
+    y, y0, dx, dx0 = layer.y_perm, clean.y_perm, layer.dx_perm, clean.dx_perm
+    assert bool(torch.isnan(y[rows(bad)]).all()) and bool(torch.isnan(dx[rows(bad)]).all())
+    assert not bool(torch.isfinite(y[rows(inf), 7]).any())
+    other = [c for c in range(cfg.d) if c != 7]
+    assert torch.equal(y[rows(inf)][:, other], y0[rows(inf)][:, other])
+    keep = [e for e in range(cfg.E) if e not in (bad, inf)]
+    for e in keep:
+        assert torch.equal(y[rows(e)], y0[rows(e)]) and torch.equal(dx[rows(e)], dx0[rows(e)]), e
+        assert torch.equal(layer.dw_gate[e], clean.dw_gate[e]) and torch.equal(layer.dw_down[e], clean.dw_down[e]), e
+    shared = slice(2 * cfg.T, 2 * cfg.T + cfg.n_shared * cfg.T)
+    assert torch.equal(y[shared], y0[shared]) and torch.equal(dx[shared], dx0[shared])
 
 
 def launches(T, d, f, E, k, local=None, S=0, backward=False):
