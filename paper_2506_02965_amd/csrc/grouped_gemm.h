@@ -268,64 +268,85 @@ struct PlanArgs {
   int32_t *pre0, *pre1, *body1, *tail1, *pre2, *order, *zero;
   int nzero;
 };
-// The plan, by one workgroup of NT threads; rows_s: 512 ints of LDS. A wavefront scans each prefix array 64 groups at
-// a time, so the plan costs one load of the offsets and two barriers.
+// The plan in pieces that need nothing of each other but the groups' row counts (512 ints of LDS, filled by plan_rows):
+// six scans (the five prefix arrays and the spread of the counts) by a wavefront each, 64 groups at a time, and the rank
+// of each group by a thread. So the plan costs one load of the offsets and a few barriers, and several small workgroups
+// can share it.
+constexpr int PLAN_SCANS = 6;
 template <int NT>
-__device__ __forceinline__ void plan_block(const PlanArgs& a, int* rows_s) {
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+__device__ __forceinline__ void plan_rows(const PlanArgs& a, int* rows_s) {
   const int G = a.Eloc + a.S;
-  if (a.zero && tid < a.nzero) a.zero[tid] = 0;
-  for (int g = tid; g < 512; g += NT)
+  for (int g = threadIdx.x; g < 512; g += NT)
     rows_s[g] = g < a.Eloc ? a.offsets[g + 1] - a.offsets[g] : g < G ? a.T : 0;
   __syncthreads();
-  for (int g = tid; g < G; g += NT) {
-    const int rows = rows_s[g];
-    int rank = 0;
-    for (int h = 0; h < G; ++h) rank += (rows_s[h] > rows) || (rows_s[h] == rows && h < g);
-    a.order[rank] = g;
-  }
-  for (int which = w; which < 6; which += NT / 64) {
-    int carry = 0, lo = 0x7fffffff, hi = 0;
-    int32_t* out = which == 0 ? a.pre0 : which == 1 ? a.pre1 : which == 2 ? a.body1 : which == 3 ? a.tail1 : a.pre2;
-    if (which < 5 && lane == 0) out[0] = 0;
-    for (int g0 = 0; g0 < G; g0 += 64) {
-      const int g = g0 + lane, rows = rows_s[g];
-      if (which == 5) {
-        if (g < G) {
-          lo = min(lo, rows);
-          hi = max(hi, rows);
-        }
-        continue;
-      }
-      const int rem = rows % a.bm1, is_tail = (rem > 0 && 2 * rem <= a.bm1) ? 1 : 0;
-      const int bm = which == 0 ? a.bm0 : which == 4 ? a.bm2 : a.bm1;
-      int v = which == 3 ? is_tail : (rows + bm - 1) / bm - (which == 2 ? is_tail : 0);
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(v, o, 64);
-        if (lane >= o) v += u;
-      }
-      v += carry;
-      carry = __builtin_amdgcn_readlane(v, 63);
-      if (g < G) out[g + 1] = v;
-    }
+}
+__device__ __forceinline__ void plan_rank(const PlanArgs& a, int g, const int* rows_s) {
+  const int G = a.Eloc + a.S;
+  if (g >= G) return;
+  const int rows = rows_s[g];
+  int rank = 0;
+  for (int h = 0; h < G; ++h) rank += (rows_s[h] > rows) || (rows_s[h] == rows && h < g);
+  a.order[rank] = g;
+}
+__device__ __forceinline__ void plan_scan(const PlanArgs& a, int which, const int* rows_s) {
+  const int G = a.Eloc + a.S, lane = threadIdx.x & 63;
+  int carry = 0, lo = 0x7fffffff, hi = 0;
+  int32_t* out = which == 0 ? a.pre0 : which == 1 ? a.pre1 : which == 2 ? a.body1 : which == 3 ? a.tail1 : a.pre2;
+  if (which < 5 && lane == 0) out[0] = 0;
+  for (int g0 = 0; g0 < G; g0 += 64) {
+    const int g = g0 + lane, rows = rows_s[g];
     if (which == 5) {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        lo = min(lo, __shfl_xor(lo, o, 64));
-        hi = max(hi, __shfl_xor(hi, o, 64));
+      if (g < G) {
+        lo = min(lo, rows);
+        hi = max(hi, rows);
       }
-      if (lane == 0) a.order[G] = (G > 0 && 4 * hi <= 5 * lo) ? 1 : 0;
+      continue;
     }
+    const int rem = rows % a.bm1, is_tail = (rem > 0 && 2 * rem <= a.bm1) ? 1 : 0;
+    const int bm = which == 0 ? a.bm0 : which == 4 ? a.bm2 : a.bm1;
+    int v = which == 3 ? is_tail : (rows + bm - 1) / bm - (which == 2 ? is_tail : 0);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(v, o, 64);
+      if (lane >= o) v += u;
+    }
+    v += carry;
+    carry = __builtin_amdgcn_readlane(v, 63);
+    if (g < G) out[g + 1] = v;
   }
+  if (which == 5) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      lo = min(lo, __shfl_xor(lo, o, 64));
+      hi = max(hi, __shfl_xor(hi, o, 64));
+    }
+    if (lane == 0) a.order[G] = (G > 0 && 4 * hi <= 5 * lo) ? 1 : 0;
+  }
+}
+// The whole plan by one workgroup of NT threads.
+template <int NT>
+__device__ __forceinline__ void plan_block(const PlanArgs& a, int* rows_s) {
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (a.zero && tid < a.nzero) a.zero[tid] = 0;
+  plan_rows<NT>(a, rows_s);
+  for (int g = tid; g < a.Eloc + a.S; g += NT) plan_rank(a, g, rows_s);
+  for (int which = w; which < PLAN_SCANS; which += NT / 64) plan_scan(a, which, rows_s);
+}
+// ... or piece `part` of plan_parts(G) of it, by a workgroup of one wavefront.
+__host__ __device__ constexpr int plan_parts(int G) { return PLAN_SCANS + (G + 63) / 64; }
+__device__ __forceinline__ void plan_part(const PlanArgs& a, int part, int* rows_s) {
+  if (part == 0 && a.zero && (int)threadIdx.x < a.nzero) a.zero[threadIdx.x] = 0;
+  plan_rows<64>(a, rows_s);
+  if (part < PLAN_SCANS) plan_scan(a, part, rows_s);
+  else plan_rank(a, 64 * (part - PLAN_SCANS) + threadIdx.x, rows_s);
 }
 __global__ __launch_bounds__(512) void tile_plan_kernel(PlanArgs a);
 
 // Few rows per expert (bf16): the forward's contractions with the weights streamed straight into registers. mt = 0: the
 // LDS tiles are the better choice (their grid has tile_grid workgroups).
 struct StreamPick {
-  int mt;     // 16-row blocks per workgroup
-  int nf;     // 16-row blocks of weights per wavefront
+  int mt;     // 16-row blocks per workgroup (1: the wavefronts work alone)
+  int nf;     // 16-column blocks of the output per wavefront
   int depth;  // K steps of weights in registers
 };
 StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid);

@@ -6,23 +6,22 @@
 // operand registers, several loads ahead, and the small register and LDS footprint leaves two and more workgroups on a
 // CU. The weights are the MFMA's first operand, the activations' rows the second, so that a lane's four accumulators
 // are four consecutive output columns of one row.
-//   * stream_split_kernel (up to 8 rows per group): 64 output columns of 16 rows, the wavefronts split K and their
-//     partial sums meet in LDS once at the end, in wavefront order (deterministic);
+//   * stream_cols_kernel (up to 8 rows per group): a wavefront owns 16 or 32 output columns of 16 rows and shares nothing;
 //   * stream_rows_kernel (up to about 100): the wavefronts split the columns and share 32, 64 or 128 rows through LDS.
+// Both sum over K in the order of the LDS tiles (one accumulator per output, 32 k per MFMA): the results are the same bits
+// whichever kernel a batch size selects.
 // The group, row chunk and columns of a workgroup come from the offsets alone (a scan over the wavefront), so no tile
-// plan has to be launched first; the plan that the backward reads is written by one extra workgroup of FWD_GU.
-// Measured (layer forward, us, LDS tiles before -> now; bound by the weights at 5.4-5.8 TB/s):
-//   T=24, d=4096, f=14336, E=8, top-2: gate/up 370 -> 334, down 301 -> 175;
-//   T=1, d=2048, f=1408, E=64, top-6, 2 shared: gate/up 29 -> 23, down 34 -> 12;
-//   T=777, d=1024, f=2816, E=16, top-2: gate/up 63 -> 58, down 62 -> 35.
+// plan has to be launched first; the plan that the backward reads is written by extra workgroups of FWD_GU.
+// Measured (layer forward, us, LDS tiles -> now):
+//   T=24, d=4096, f=14336, E=8, top-2: gate/up 350 -> 310, down 279 -> 171 (bound by the weights, 5.4-5.8 TB/s);
+//   T=1, d=2048, f=1408, E=64, top-6, 2 shared: gate/up 29 -> 19, down 34 -> 12 (4.8 and 3.9 TB/s).
+//   T=777, d=1024, f=2816, E=16, top-2: gate/up 58 -> 52, down 61 -> 33 (3.5 and 2.8 TB/s).
 #include "grouped_gemm.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace pcmoe {
-
-constexpr int ST_COLS = 64;         // output columns (FWD_GU: 32 gate and 32 up columns) of a K-splitting workgroup
-constexpr int ST_KS = 4;            // its wavefronts
 
 // Workgroup -> (group, row chunk of `chunk` rows, column block). Lane l of a wavefront counts the chunks of the groups
 // [l NS, l NS + NS) (one batch of loads), a scan over the lanes finds the lane whose groups hold the tile, and its
@@ -94,99 +93,83 @@ __device__ __forceinline__ void store_out(const GemmArgs& p, size_t row, int col
   *reinterpret_cast<uint2*>((bf16*)p.out + row * p.d + col) = pack4(v);
 }
 
-// Up to 16 rows of a group: the wavefronts split K. KIND FWD_GU or FWD_DOWN.
-template <int KIND>
-__global__ __launch_bounds__(64 * ST_KS) void stream_split_kernel(GemmArgs p, PlanArgs plan, int n_blocks, int tiles) {
-  constexpr int NF = ST_COLS / 16, KS = ST_KS;
-  constexpr int PITCH = ST_COLS + 4;
-  __shared__ __align__(16) float red[KS * 16 * PITCH];
-  static_assert(sizeof(red) >= 512 * sizeof(int), "the plan keeps its row counts here");
+// Up to 16 rows of a group, KIND FWD_GU or FWD_DOWN: a workgroup is one wavefront, which owns 16 M weight rows (FWD_GU:
+// 16 M gate rows and the same up rows) over the whole K and reads them and the group's rows straight into MFMA operands,
+// D steps of 64 k ahead. Bound by the round trips of a wavefront's loads as long as few groups are active, then by the
+// weights: single wavefronts spread evenly over the CUs and wait for no one (T = 1 of the 64-expert layer above: gate/up
+// 19 us, 23 by workgroups of four). M = 2 halves the reads of the rows, which matter from a few rows per group on; it
+// leaves half the wavefronts. (A split of K over four wavefronts, summed through LDS, took 23 and 12 us there and 84 and
+// 63, now 82 and 49, at T = 1 of 8 experts, d = 4096, f = 14336; and its results were other bits than the tiles'.)
+template <int KIND, int M, int D>
+__global__ __launch_bounds__(64, 2) void stream_cols_kernel(GemmArgs p, PlanArgs plan, int n_blocks, int tiles) {
+  constexpr int NF = KIND == FWD_GU ? 2 * M : M;
   if (KIND == FWD_GU && (int)blockIdx.x >= tiles) {
-    plan_block<64 * KS>(plan, (int*)red);
+    __shared__ int rows_s[512];
+    plan_part(plan, blockIdx.x - tiles, rows_s);
     return;
   }
   StreamTile t;
   if (!stream_decode(p, blockIdx.x, 16, n_blocks, t)) return;
   const int lane = threadIdx.x & 63, q = lane >> 4, li = lane & 15;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int K = KIND == FWD_GU ? p.d : p.f;
+  const int K = KIND == FWD_GU ? p.d : p.f, KB = K * 2, units = K / 64;
   const bool routed = t.g < p.Eloc;
   // rows of the activations: x_perm / H rows of a routed group, x / H rows of a shared expert
   const size_t rs = routed ? (size_t)t.row0 : (size_t)p.rows_cap + (size_t)(t.g - p.Eloc) * p.T;
-  const char* xb = KIND == FWD_GU ? (routed ? (const char*)p.xp + (size_t)t.row0 * K * 2 : (const char*)p.x)
-                                  : (const char*)p.h + rs * K * 2;
+  const char* xb = KIND == FWD_GU ? (routed ? (const char*)p.xp + (size_t)t.row0 * KB : (const char*)p.x)
+                                  : (const char*)p.h + rs * KB;
   const int m0 = t.ch * 16, m_rows = min(t.rows - m0, 16);
-  const auto xr = buf_rsrc(xb + (size_t)m0 * K * 2, (size_t)m_rows * K * 2);
-  // weight rows of the column block: FWD_GU 32 gate rows and the same 32 up rows, FWD_DOWN 64 rows of W_down
+  const auto xr = buf_rsrc(xb + (size_t)m0 * KB, (size_t)m_rows * KB);
   const size_t wsz = (size_t)p.d * p.f * 2;
-  const int wrow = t.nb * (KIND == FWD_GU ? ST_COLS / 2 : ST_COLS);
-  const char* w0 = (const char*)(KIND == FWD_GU ? p.wg : p.wd) + t.g * wsz + (size_t)wrow * K * 2;
-  const char* w1 = KIND == FWD_GU ? (const char*)p.wu + t.g * wsz + (size_t)wrow * K * 2 : w0;
-  constexpr int F0 = KIND == FWD_GU ? NF / 2 : NF;  // weight blocks read through the first resource
-  const auto wr0 = buf_rsrc(w0, (size_t)16 * F0 * K * 2);
-  const auto wr1 = buf_rsrc(w1, (size_t)16 * F0 * K * 2);
+  const int wrow = t.nb * 16 * M;  // first output column and weight row
+  const char* w0 = (const char*)(KIND == FWD_GU ? p.wg : p.wd) + t.g * wsz + (size_t)wrow * KB;
+  const char* w1 = KIND == FWD_GU ? (const char*)p.wu + t.g * wsz + (size_t)wrow * KB : w0;
+  const auto wr0 = buf_rsrc(w0, (size_t)16 * M * KB);
+  const auto wr1 = buf_rsrc(w1, (size_t)16 * M * KB);
 
-  const int units = K / 64, rounds = (units + KS - 1) / KS;
-  const int lane_off = li * K * 2 + q * 16;
   floatx4 acc[NF];
 #pragma unroll
   for (int i = 0; i < NF; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-  Chunk wb[2][NF][2], xv[2][2];
-  // step r of this wavefront: bytes [128 u, 128 u + 128) of each row, u = r KS + w (zeros past the last unit)
-  auto load = [&](int r, Chunk(&wbuf)[NF][2], Chunk(&xbuf)[2]) {
-    const int u = r * KS + w;
-    const int vo = u < units ? lane_off + u * 128 : kBufPast;
+  Chunk wb[D][NF][2], xv[D][2];
+  // step u: bytes [128 u, 128 u + 128) of each row (zeros past the last)
+  auto load = [&](int u, Chunk(&wbuf)[NF][2], Chunk(&xbuf)[2]) {
+    const int vo = li * KB + q * 16 + u * 128;
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const int o = vo + (i % F0) * 16 * K * 2 * (u < units ? 1 : 0);
+    for (int h = 0; h < 2; ++h) xbuf[h] = buf_ld16(xr, u < units ? vo + 64 * h : kBufPast);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) wbuf[i][h] = buf_ld16(i < F0 ? wr0 : wr1, o + 64 * h);
-    }
+    for (int i = 0; i < NF; ++i)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) xbuf[h] = buf_ld16(xr, vo + 64 * h);
+      for (int h = 0; h < 2; ++h)
+        wbuf[i][h] = buf_ld16(i < M ? wr0 : wr1, u < units ? vo + (i % M) * 16 * KB + 64 * h : kBufPast);
   };
-  auto mul = [&](const Chunk(&wbuf)[NF][2], const Chunk(&xbuf)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < NF; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wbuf[i][h]),
-                                                         __builtin_bit_cast(bf16x8, xbuf[h]), acc[i], 0, 0, 0);
-  };
-  // the scheduling barriers keep each step's loads behind the MFMAs before them: left alone, the compiler gathers both
+  // the scheduling barriers keep each step's loads behind the MFMAs before them: left alone, the compiler gathers the
   // steps' loads at the loop's end and waits for all of them at its top
-  load(0, wb[0], xv[0]);
-  __builtin_amdgcn_sched_barrier(0);
-  load(1, wb[1], xv[1]);
-  __builtin_amdgcn_sched_barrier(0);
-  for (int r = 0; r < rounds; r += 2) {
-    mul(wb[0], xv[0]);
-    __builtin_amdgcn_sched_barrier(0);
-    load(r + 2, wb[0], xv[0]);
-    __builtin_amdgcn_sched_barrier(0);
-    mul(wb[1], xv[1]);
-    __builtin_amdgcn_sched_barrier(0);
-    load(r + 3, wb[1], xv[1]);
+#pragma unroll
+  for (int s = 0; s < D; ++s) {
+    load(s, wb[s], xv[s]);
     __builtin_amdgcn_sched_barrier(0);
   }
-
-  // Sum over the wavefronts in their order and write out: thread -> (row, 4 columns).
+  for (int u0 = 0; u0 < units; u0 += D) {
 #pragma unroll
-  for (int i = 0; i < NF; ++i) *reinterpret_cast<floatx4*>(&red[(w * 16 + li) * PITCH + 16 * i + 4 * q]) = acc[i];
-  __syncthreads();
-  constexpr int QC = (KIND == FWD_GU ? ST_COLS / 2 : ST_COLS) / 4;  // column quads of the outputs
-  const int rr = threadIdx.x / QC, c = (threadIdx.x % QC) * 4;
-  if (rr >= m_rows) return;
-  floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f}, u = v;
+    for (int s = 0; s < D; ++s) {
 #pragma unroll
-  for (int k = 0; k < KS; ++k) {
-    const float* src = &red[(k * 16 + rr) * PITCH + c];
-    v += *reinterpret_cast<const floatx4*>(src);
-    if (KIND == FWD_GU) u += *reinterpret_cast<const floatx4*>(src + ST_COLS / 2);
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wb[s][i][h]),
+                                                           __builtin_bit_cast(bf16x8, xv[s][h]), acc[i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      load(u0 + s + D, wb[s], xv[s]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
-  const size_t row = rs + m0 + rr;
-  if (KIND == FWD_GU) store_gu(p, row, wrow + c, v, u);
-  else store_out(p, row, wrow + c, v);
+  // lane (q, li), block i: columns 16 i + 4 q .. 16 i + 4 q + 3 of row li
+  if (li >= m_rows) return;
+  const size_t row = rs + m0 + li;
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    if (KIND == FWD_GU) store_gu(p, row, wrow + 16 * i + 4 * q, acc[i], acc[NF - M + i]);
+    else store_out(p, row, wrow + 16 * i + 4 * q, acc[i]);
+  }
 }
 
 // Up to 16 MT rows of a group: the wavefronts share the rows and split the columns.
@@ -420,14 +403,15 @@ static long chunk_bound(const moe_desc& d, int chunk) {
 
 static unsigned grid_of(long wgs) { return (unsigned)((wgs + 7) / 8 * 8); }
 
-template <int KIND>
-static hipError_t run_split(const moe_desc& d, const GemmArgs& a, const PlanArgs& plan, hipStream_t s,
-                            const char* name) {
-  const int n_blocks = KIND == FWD_GU ? d.d_ff / (ST_COLS / 2) : d.d_model / ST_COLS;
+template <int KIND, int M, int D>
+static hipError_t run_cols(const moe_desc& d, const GemmArgs& a, const PlanArgs& plan, hipStream_t s,
+                           const char* name) {
+  const int n_blocks = (KIND == FWD_GU ? d.d_ff : d.d_model) / (16 * M);
   const unsigned tiles = grid_of(chunk_bound(d, 16) * n_blocks);
+  const unsigned extra = KIND == FWD_GU ? plan_parts(d.local_count + d.n_shared) : 0;
   KernelTimer kt(name, s);
-  hipLaunchKernelGGL((stream_split_kernel<KIND>), dim3(tiles + (KIND == FWD_GU ? 1 : 0)), dim3(64 * ST_KS), 0, s, a,
-                     plan, n_blocks, (int)tiles);
+  hipLaunchKernelGGL((stream_cols_kernel<KIND, M, D>), dim3(tiles + extra), dim3(64), 0, s, a, plan, n_blocks,
+                     (int)tiles);
   return hipGetLastError();
 }
 template <int KIND, int MT, int NF, int D>
@@ -457,8 +441,12 @@ static GroupRows group_rows(const moe_desc& d) {
 // tiles over 40 layers (d 256 to 4096, f 512 to 14336, 3 to 128 groups, with and without shared experts, whole layers
 // and shards) at 1 to 200 rows per group, spread uniformly, Zipf-skewed (exponent 1.1) and with one expert in every
 // token; no call was more than 2% slower than on the tiles. Times are tiles -> streamed, us, uniform and skewed rows:
-//   * up to 8 rows, at most 5 workgroups per CU: the split over K (2-20% under the 32-row kernel, which is 5-20%
-//     under it beyond 5 per CU);
+//   * up to 8 rows: the single wavefronts, as long as they are at most 10 per CU for gate/up and 20 for the down
+//     projection (at twice as many the 32-row chunks are 5-15% faster). Two column blocks each past 2 rows in gate/up (d =
+//     4096, f = 2816, 8 experts: 2 rows 72 us either way, 8 rows 83 and 79) and past one row in the down projection where
+//     that leaves a wavefront per CU (d = 1024, f = 2816, 16 experts, 8 rows: 22.5 and 19.2). Where the experts with a row
+//     fill 1.6 workgroups per CU, the 32-row chunks of the down projection are as fast or faster (d = 2048, f = 8192, 16
+//     experts, 8 rows: 127 and 108; d = 4096, f = 14336, 8 experts, 6 rows: 185 and 172; d = 4096, f = 2816: 45 and 37);
 //   * up to 24, 50 and 100 rows: 32-, 64- and 128-row chunks (the next size up costs 5-30% more below each line, the
 //     previous one 5-50% above it). A shard takes the size for twice its even share;
 //   * where the tiles would leave half the CUs or more idle, chunks up to 200 rows: 10-60% faster, skewed or not;
@@ -478,14 +466,18 @@ static GroupRows group_rows(const moe_desc& d) {
 // 83 -> 60 us), and 8 steps in flight in place of 4 up to two per CU (f = 8192, 12 rows: 55 -> 49 us; f = 2816, d = 1024:
 // 25 -> 22; 128 experts, d = 512, are 10% slower with 8).
 StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid) {
-  const StreamPick none{0, 0, 0}, split{1, 1, 2};
+  const StreamPick none{0, 0, 0};
   if (d.dtype != MOE_BF16) return none;
   const int G = d.local_count + d.n_shared;
   const GroupRows gr = group_rows(d);
   const double rows = std::min(2 * gr.mean, gr.most);
   const int cols = kind == FWD_GU ? d.d_ff : d.d_model, cus = device_cus();
-  const long split_wgs = chunk_bound(d, 16) * (cols / (kind == FWD_GU ? ST_COLS / 2 : ST_COLS));
-  if (rows <= 8 && split_wgs <= 5L * cus) return split;
+  if (rows <= 8 && chunk_bound(d, 16) * (cols / 16) <= (kind == FWD_GU ? 10L : 20L) * cus) {
+    if (kind == FWD_GU) return rows <= 2 ? StreamPick{1, 1, 4} : StreamPick{1, 2, 2};
+    const double active = d.local_count * (1 - std::pow(1 - (double)d.top_k / d.n_experts, d.T)) + d.n_shared;
+    if (active * (cols / 64) < 1.6 * cus) return StreamPick{1, rows > 1 && active * (cols / 32) >= cus ? 2 : 1, 4};
+    return StreamPick{2, 1, d.d_ff >= 1024 ? 8 : 4};
+  }
   if (tile_grid <= cus / 2) {
     if (gr.mean > 200) return none;
   } else {
@@ -509,7 +501,7 @@ StreamPick stream_pick(const moe_desc& d, int kind, long tile_grid) {
 hipError_t stream_gate_up(const moe_desc& d, const StreamPick& k, const GemmArgs& a, const PlanArgs& plan,
                           hipStream_t s, const char* name) {
   switch (k.mt) {
-    case 1: return run_split<FWD_GU>(d, a, plan, s, name);
+    case 1: return k.nf == 2 ? run_cols<FWD_GU, 2, 2>(d, a, plan, s, name) : run_cols<FWD_GU, 1, 4>(d, a, plan, s, name);
     case 2: return run_rows<FWD_GU, 2, 2, 4>(d, a, plan, s, name);
     case 4: return run_rows<FWD_GU, 4, 2, 4>(d, a, plan, s, name);
     default: return run_rows<FWD_GU, 8, 2, 2>(d, a, plan, s, name);
@@ -518,7 +510,7 @@ hipError_t stream_gate_up(const moe_desc& d, const StreamPick& k, const GemmArgs
 hipError_t stream_down(const moe_desc& d, const StreamPick& k, const GemmArgs& a, hipStream_t s, const char* name) {
   const PlanArgs none{};
   switch (k.mt) {
-    case 1: return run_split<FWD_DOWN>(d, a, none, s, name);
+    case 1: return k.nf == 2 ? run_cols<FWD_DOWN, 2, 4>(d, a, none, s, name) : run_cols<FWD_DOWN, 1, 4>(d, a, none, s, name);
     case 2:
       return k.depth == 8 ? run_rows<FWD_DOWN, 2, 1, 8>(d, a, none, s, name)
                           : run_rows<FWD_DOWN, 2, 1, 4>(d, a, none, s, name);

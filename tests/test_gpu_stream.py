@@ -27,7 +27,7 @@ def _case(T, d, f, E, edges, seed, **kw):
 
 
 CASES = {
-    # expected rows per group <= 8: the K-splitting kernel (16-row chunks)
+    # expected rows per group <= 8: single wavefronts (16-row chunks), one or two column blocks each
     "split": _case(48, 256, 384, 16, [0, 1, 15, 16, 17, 33, 0], 71),
     "split_k_remainder_shared": _case(24, 128, 128, 12, [16, 0, 17], 72, n_shared=2),
     "split_66_groups": _case(130, 128, 256, 64, [0, 16, 1, 40], 73, n_shared=2),
@@ -50,6 +50,10 @@ CASES = {
     # more than 128 groups: a lane of the group scan counts eight of them
     "split_130_groups": _case(300, 128, 128, 130, [0, 16, 17, 40, 1], 95),
     "split_258_groups": _case(64, 128, 256, 256, [0, 17, 33, 1], 96, n_shared=2),
+    # one column block of a few rows; two blocks in the down projection; its 32-row chunks where many experts are active
+    "one_block": _case(16, 256, 384, 16, [0, 16, 1, 3], 97),
+    "down_two_blocks": _case(96, 2048, 128, 24, [0, 16, 17, 31, 1], 98),
+    "down_rows32_many": _case(40, 2048, 1024, 16, [0, 16, 17, 33, 1], 99),
 }
 
 
@@ -121,6 +125,31 @@ def test_non_finite_weights_stay_in_their_rows(name):
         assert torch.equal(layer.dw_gate[e], clean.dw_gate[e]) and torch.equal(layer.dw_down[e], clean.dw_down[e]), e
     shared = slice(2 * cfg.T, 2 * cfg.T + cfg.n_shared * cfg.T)
     assert torch.equal(y[shared], y0[shared]) and torch.equal(dx[shared], dx0[shared])
+
+
+@pytest.mark.parametrize("d,f,E,k,S", [(256, 384, 16, 2, 1), (512, 1408, 40, 4, 0), (4096, 1024, 8, 2, 0)])
+def test_forward_bits_do_not_depend_on_the_batch(d, f, E, k, S):
+    """A token's expert outputs are the same bits whatever kernel its batch's size selects: single wavefronts, 32-, 64-
+    and 128-row chunks and the LDS tiles sum over K in one order."""
+    log(f"[stream] bits over batch sizes, d={d} f={f} E={E}")
+    sizes = (1, 7, 24, 70, 200, 500, 4096)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    new = lambda *s, std=1.0: (torch.randn(*s, device="cuda", generator=gen) * std).to(torch.bfloat16)
+    G = E + S
+    x, w_router = new(max(sizes), d), new(E, d, std=d ** -0.5)
+    wg, wu, wd = new(G, f, d, std=d ** -0.5), new(G, f, d, std=d ** -0.5), new(G, d, f, std=f ** -0.5)
+    out = {}
+    for T in sizes:
+        layer = MoELayer(LayerConfig("bits", T=T, d=d, f=f, E=E, k=k, n_shared=S, backward=False))
+        layer.forward(LayerWeights(x[:T].contiguous(), w_router, None, 1, wg, wu, wd))
+        torch.cuda.synchronize()
+        rows = layer.slot_to_row.long().view(T, k)
+        shared = T * k + T * torch.arange(S, device="cuda")[None] + torch.arange(T, device="cuda")[:, None]
+        out[T] = (layer.topk_idx.clone(), layer.y_perm[torch.cat([rows, shared], 1)].clone())
+    ref_idx, ref = out[max(sizes)]
+    for T, (idx, y) in out.items():
+        assert torch.equal(idx, ref_idx[:T]), T
+        assert torch.equal(y, ref[:T]), T
 
 
 def launches(T, d, f, E, k, local=None, S=0, backward=False):
