@@ -42,7 +42,8 @@ GEMM_FLOPS_PER_ROW_DF = {
 COPY_CAL_BYTES = 256 << 20   # bytes read (and written) by one calibration copy
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_dominant_kernel.txt")
 GEMM_SOURCES = [os.path.join(ROOT, "paper_2506_02965_amd", "csrc", n)
-                for n in ("grouped_gemm_bf16.hip", "grouped_gemm.h", "pcmoe_internal.h")]
+                for n in ("grouped_gemm_bf16.hip", "stream_gemm_bf16.hip", "grouped_gemm_f32.hip", "grouped_gemm.h",
+                          "pcmoe_internal.h")]
 
 
 def gemm_source_digest():

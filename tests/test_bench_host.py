@@ -44,6 +44,23 @@ def test_hbm_step_bytes_by_hand():
     assert out["unpermute"]["bytes"] == 16 * row + 8 * row + 8 * row + 4 * 8 * 2
 
 
+def test_hbm_step_of_the_fused_dispatch():
+    """A few thousand slots dispatch in one launch: the same bytes over that launch's time."""
+    cfg = LayerConfig("b", T=8, d=16, f=32, E=4, k=2)
+    out = bench.hbm_steps(cfg, 16, {"permute_fused": {"avg_us": 2.0}})
+    assert out["permute"]["bytes"] == 8 * 32 + 16 * 32 + 8 * 8 * 2
+    assert out["permute"]["us"] == 2.0
+    assert bench.hbm_steps(cfg, 16, {"permute_hist": {"avg_us": 1.0}}).get("permute") is None   # not all three launches
+
+
+def test_gemm_sources_are_all_that_launch_the_recorded_kernels():
+    """A traffic record is stale once any source of a kernel recorded under an expert-GEMM name has changed: the files
+    that use the grouped-GEMM header, and the headers."""
+    csrc = os.path.join(ROOT, "paper_2506_02965_amd", "csrc")
+    users = {n for n in os.listdir(csrc) if n.endswith(".hip") and '"grouped_gemm.h"' in open(os.path.join(csrc, n)).read()}
+    assert {os.path.basename(p) for p in bench.GEMM_SOURCES} == users | {"grouped_gemm.h", "pcmoe_internal.h"}
+
+
 def test_traffic_record_matches_only_its_kernel_workload_and_sources():
     rec = {}
     for line in open(bench.TRAFFIC_FILE):
