@@ -340,7 +340,6 @@ __device__ __forceinline__ void plan_part(const PlanArgs& a, int part, int* rows
   if (part < PLAN_SCANS) plan_scan(a, part, rows_s);
   else plan_rank(a, 64 * (part - PLAN_SCANS) + threadIdx.x, rows_s);
 }
-__global__ __launch_bounds__(512) void tile_plan_kernel(PlanArgs a);
 
 // Few rows per expert (bf16): the forward's contractions with the weights streamed straight into registers. mt = 0: the
 // LDS tiles are the better choice (their grid has tile_grid workgroups).

@@ -938,6 +938,12 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// The tile plan in a launch of its own, bf16 and fp32 layers (a streamed gate/up launch writes it itself).
+__global__ __launch_bounds__(512) void tile_plan_kernel(PlanArgs a) {
+  __shared__ int rows_s[512];
+  plan_block<512>(a, rows_s);
+}
+
 // Zeroes the tickets of the paired launches that follow on the stream.
 __global__ void zero_tickets_kernel(int* p, int n) {
   if ((int)threadIdx.x < n) p[threadIdx.x] = 0;

@@ -273,13 +273,6 @@ __global__ __launch_bounds__(C::NT) void gemm_f32_kernel(GemmArgs pa, GemmArgs p
   else gemm_tile_f32<KB>(pb, bid - grid_a, smem);
 }
 
-// m-tile prefixes over groups for two tile heights: pre[g] = sum_{g' < g} ceil(rows_g' / bm); and
-// the groups ordered by decreasing row count (ties by index).
-__global__ __launch_bounds__(512) void tile_plan_kernel(PlanArgs a) {
-  __shared__ int rows_s[512];
-  plan_block<512>(a, rows_s);
-}
-
 // ------------------------------------------------------------------------- host side
 
 static int round8(long v) { return (int)((v + 7) / 8 * 8); }

@@ -175,8 +175,9 @@ __global__ __launch_bounds__(64, 2) void stream_cols_kernel(GemmArgs p, PlanArgs
 // Up to 16 MT rows of a group: the wavefronts share the rows and split the columns.
 //   * each of the 4 wavefronts owns 16 NF weight rows (FWD_GU: 16 gate rows and the same 16 up rows) over the whole K
 //     and keeps D steps of 64 k of them in flight in registers;
-//   * the group's rows (up to 16 MT) pass through LDS, 64 k at a time in two stages, filled from registers loaded two
-//     steps ahead: one barrier per step, and no load is waited for in the step that issues it;
+//   * the group's rows (up to 16 MT) pass through LDS, 64 k at a time in two stages, filled from registers that are
+//     loaded D - 1 steps before they are put there: one barrier per step. With D > 2 no load is waited for in the step
+//     that issues it; with D = 2 (gate/up of 128 rows) the next step's rows are, at the step's end;
 //   * the accumulators hold four consecutive output columns of one row per lane, so SwiGLU and the stores need no LDS.
 // X stage: 128-byte rows, 16-byte chunk c of row r at c ^ swz(r).
 __device__ __forceinline__ int xs_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
