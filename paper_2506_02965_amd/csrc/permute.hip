@@ -194,7 +194,8 @@ __global__ __launch_bounds__(256) void perm_gather_kernel(int Tn, int k, int cpr
 // workgroup of 16 wavefronts ranks all the slots itself (wavefront w the slots [64 ITERS w, 64 ITERS (w + 1)), one ballot
 // pass, stable), so no workgroup waits for another; it then gathers its own tokens, whose first chunks are loaded ahead
 // of the ranking. Workgroup 0 also writes counts, offsets and both maps. Bound by the launch and the ranking's chain of
-// ballots: 6 to 1,800 slots 13.6-15.8 -> 8.2-9.5 us a call (the call's host side is most of the rest).
+// ballots: 6 to 4,000 slots 13.5-14.2 -> 8.2-9.0 us a call, calls back to back (the kernel alone takes 4 to 12, mostly under
+// the host side of the next call).
 constexpr int PS_WAVES = 16;
 template <int ITERS>
 __global__ __launch_bounds__(64 * PS_WAVES) void perm_small_kernel(const int32_t* __restrict__ idx, int Tn, int k, int lb,
