@@ -77,10 +77,16 @@ __global__ __launch_bounds__(256) void combine_kernel(int Tn, int k, int S, int 
   }
 }
 
-// The y_perm rows are read here for the last time, and nearly as many bytes are written beside them: read non-temporal,
-// they leave the last-level cache to the writes (T = 16384, d = 2048, top-6: 159 -> 144 us; T = 8192, top-8: 110 -> 94;
-// the same for the combine's reads, which this kernel repeats, or the hand-back's, moved the time to the next kernel).
-template <typename T, int KM, int CPL>
+// The y_perm rows are read here for the last time, and nearly as many bytes are written beside them: where both outgrow
+// the last-level cache (NT, launch_combine_bwd) they are read non-temporal and leave it to the writes (the same for the
+// combine's reads, which this kernel repeats, or the hand-back's, moved the time to the next kernel).
+template <bool NT>
+__device__ __forceinline__ Chunk ld_row_chunk(const Chunk* p) {
+  if constexpr (NT) return ld_chunk_nt(p);
+  return ld_chunk(p);
+}
+
+template <typename T, int KM, int CPL, bool NT>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(int Tn, int k, int cpr, const Chunk* __restrict__ dy,
                                                           const Chunk* __restrict__ yp,
                                                           const int32_t* __restrict__ s2r,
@@ -107,7 +113,8 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(int Tn, int k, int cpr
       for (int j = 0; j < KM; ++j)
 #pragma unroll
         for (int u = 0; u < CPL; ++u)
-          in[j][u] = (rows[j] >= 0 && c0 + 64 * u < cpr) ? ld_chunk_nt(yp + (size_t)rows[j] * cpr + c0 + 64 * u) : zero_chunk();
+          in[j][u] = (rows[j] >= 0 && c0 + 64 * u < cpr) ? ld_row_chunk<NT>(yp + (size_t)rows[j] * cpr + c0 + 64 * u)
+                                                         : zero_chunk();
 #pragma unroll
       for (int u = 0; u < CPL; ++u) {
         const int c = c0 + 64 * u;
@@ -157,14 +164,20 @@ hipError_t launch_combine_bwd(const moe_desc& d, const void* dy, const void* yp,
                               const float* w, void* dyp, float* dgate, hipStream_t s) {
   const int cpr = (int)(d.d_model * elem_bytes(d) / 16);
   KernelTimer kt("combine_bwd", s);
+  // Non-temporal reads from 128 MiB of routed rows: with the rows written they are then the 256 MB of the last-level
+  // cache. Below that y_perm is still there from the forward and plain reads hit it. Measured, plain and non-temporal:
+  // 49 MB (T = 3000, d = 1024, top-8, bf16) 18.3 and 21.4 us, 98 MB (d = 2048) 34.3 and 41.4, 131 MB (T = 1000,
+  // d = 4096, top-8, fp32) 49.3 and 49.2, 134 MB (T = 8192, d = 4096, top-2) 70 and 52, 201 MB (d = 2048, top-6) 92
+  // and 73, 268 MB (top-8) 120 and 104; T = 16384, top-6 159 and 144.
+  const bool nt = (size_t)d.T * d.top_k * cpr * 16 >= (size_t)128 << 20;
   row_dispatch(d.top_k, cpr, [&](auto km, auto cpl) {
     constexpr int KM = decltype(km)::value, CPL = decltype(cpl)::value;
-    if (d.dtype == MOE_BF16)
-      hipLaunchKernelGGL((combine_bwd_kernel<bf16, KM, CPL>), dim3(token_blocks(d.T)), dim3(256), 0, s, d.T,
-                         d.top_k, cpr, (const Chunk*)dy, (const Chunk*)yp, s2r, w, (Chunk*)dyp, dgate);
-    else
-      hipLaunchKernelGGL((combine_bwd_kernel<float, KM, CPL>), dim3(token_blocks(d.T)), dim3(256), 0, s, d.T,
-                         d.top_k, cpr, (const Chunk*)dy, (const Chunk*)yp, s2r, w, (Chunk*)dyp, dgate);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(token_blocks(d.T)), dim3(256), 0, s, d.T, d.top_k, cpr, (const Chunk*)dy,
+                         (const Chunk*)yp, s2r, w, (Chunk*)dyp, dgate);
+    };
+    if (d.dtype == MOE_BF16) go(nt ? combine_bwd_kernel<bf16, KM, CPL, true> : combine_bwd_kernel<bf16, KM, CPL, false>);
+    else go(nt ? combine_bwd_kernel<float, KM, CPL, true> : combine_bwd_kernel<float, KM, CPL, false>);
   });
   return hipGetLastError();
 }
