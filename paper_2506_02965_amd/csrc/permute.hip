@@ -671,7 +671,12 @@ hipError_t launch_permute_bwd(const moe_desc& d, const void* dxp, const int32_t*
   KernelTimer kt("unpermute", s);
   // Without renormalisation every expert's gradient is nonzero. Up to 8 experts the first round trip of the walk takes
   // most of them (9 experts, T = 777, d = 4096: 13.6 us by the walk, 12.9 by the product; 16, T = 16384: 83 and 71).
-  if (dl && !d.renormalize && d.n_experts > 8)
+  // The product costs as much for 9 experts as for 16: below 12, long bf16 rows of few slots walk (us for walk / product:
+  // T = 8192, d = 4096, top-1 9 experts 34 / 43, 10 38 / 43, 12 41 / 40; 9 experts, T = 16384, d = 2048 top-2 39 / 44;
+  // T = 8192, d = 1024, top-2 17.8 / 14.7; fp32 39 / 36 at T = 8192, d = 2048, top-2).
+  const bool walk = d.n_experts <= 8 || (d.n_experts < 12 && d.dtype == MOE_BF16 && d.top_k <= 2 && d.d_model >= 2048 &&
+                                         d.T >= 2048);
+  if (dl && !d.renormalize && !walk)
     return d.dtype == MOE_BF16 ? unpermute_dense<bf16>(d, cpr, dxp, s2r, dl, wr, dx, s)
                                : unpermute_dense<float>(d, cpr, dxp, s2r, dl, wr, dx, s);
   batch_dispatch(d.top_k, d.n_shared, dl != nullptr, [&](auto km, auto sm, auto has_dl) {
