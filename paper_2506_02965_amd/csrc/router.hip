@@ -4,7 +4,8 @@
 // fp32. The order of a score's sum follows the tiling, which goes by the batch size and the device's CU count: equal
 // calls give equal bits, and where fp64 holds the sum exactly (bf16 inputs, as long as no product is smaller than about
 // 2^-37 of the sum) so do other batches; else a score can differ in its last fp32 bit, in about one of 10^8, and a
-// selection that hangs on that bit with it. Selection happens at wavefront level: k rounds of a 64-lane maximum over order-preserving keys, ties to the lowest expert index.
+// selection that hangs on that bit with it. Selection happens at wavefront level: k rounds of a 64-lane maximum over
+// order-preserving keys, ties to the lowest expert index.
 #include "pcmoe_internal.h"
 #include <math.h>
 #include <algorithm>
@@ -257,11 +258,19 @@ static hipError_t route_fwd_t(const moe_desc& d, const void* x, const void* wr, 
   // its padded tokens' products and a second round costs as much as the first. Measured on MI355X (d = 2048, E = 64;
   // us for 1 / 4 / 16 / 32 tokens): T = 24 12 / 14 / - / -, T = 300 22 / 15 / 26 / 43, T = 3000 - / 48 / 26 / 43,
   // T = 8192 - / - / 50 / 44; the 16-token workgroups of 4 wavefronts used before took 36, 37, 37 and 57.
-  // Wavefronts: as many as fit the LDS table and, at 16 of them, 128 VGPRs without spills.
+  // Past one round of 32 tokens a full one costs 0.9 of two rounds of 16, but a last round that is nearly empty as much
+  // as a full one: 32 tokens are taken while their rounds cost less (bf16, E = 64, d = 2048, us for 16 / 32 tokens:
+  // T = 8300 68 / 80, 12,288 69 / 80, 16,384 88 / 82, 16,500 108 / 119, 24,576 128 / 121). With up to 32 bf16 experts
+  // 16 tokens of 4 wavefronts are always the better past one round (E = 32, T = 16,384, d = 128: 12.1 / 15.3, T = 8300,
+  // d = 2048: 36 / 47).
+  // Wavefronts: as many as fit the LDS table and, at 16 of them, 128 VGPRs without spills; 4 to a workgroup of 16 tokens
+  // in long batches, where several workgroups share a CU.
 #define RT(TB, TT, NET, WE, WK, PF) \
   return route_fwd_run<T, TB, TT, NET, WE, WK, PF>(d, x, wr, bias, div, logits, idx, w, s)
   const int cus = device_cus();
-  const int tok = d.T <= cus ? 1 : d.T <= 4 * cus ? 4 : d.T <= 16 * cus ? 16 : 32;
+  const int r16 = (d.T + 16 * cus - 1) / (16 * cus), r32 = (r16 + 1) / 2;  // rounds of 16 and of 32 tokens per CU
+  const bool by32 = r32 == 1 || ((E > 32 || d.dtype == MOE_F32) && 20 * r32 <= 11 * r16);
+  const int tok = d.T <= cus ? 1 : d.T <= 4 * cus ? 4 : r16 == 1 ? 16 : by32 ? 32 : 64;  // 64: 16, in a long batch
   if (E <= 16) {
     if (tok == 1) RT(1, 1, 1, 1, 16, 4);
     if (tok == 4) RT(4, 1, 1, 1, 16, 4);
@@ -271,22 +280,24 @@ static hipError_t route_fwd_t(const moe_desc& d, const void* x, const void* wr, 
     if (tok == 1) RT(1, 1, 2, 1, 16, 4);
     if (tok == 4) RT(4, 1, 2, 1, 16, 4);
     if (tok == 16) RT(16, 1, 2, 1, 8, 3);
-    RT(16, 2, 2, 1, 8, 2);
+    if (tok == 32) RT(16, 2, 2, 1, 8, 2);
+    RT(16, 1, 2, 1, 4, 4);
   } else if (E <= 64) {
     if (tok == 1) RT(1, 1, 4, 1, 16, 2);
     if (tok == 4) RT(4, 1, 4, 1, 16, 2);
     if (tok == 16) RT(16, 1, 4, 1, 8, 2);
-    RT(16, 2, 4, 1, 8, 2);
+    if (tok == 32) RT(16, 2, 4, 1, 8, 2);
+    RT(16, 1, 4, 1, 4, 2);
   } else if (E <= 128) {
     if (tok == 1) RT(1, 1, 4, 2, 8, 2);
     if (tok == 4) RT(4, 1, 4, 2, 8, 2);
-    if (tok == 16) RT(16, 1, 4, 2, 4, 2);
-    RT(16, 2, 4, 2, 4, 2);
+    if (tok == 32) RT(16, 2, 4, 2, 4, 2);
+    RT(16, 1, 4, 2, 4, 2);
   } else {
     if (tok == 1) RT(1, 1, 4, 4, 4, 2);
     if (tok == 4) RT(4, 1, 4, 4, 4, 2);
-    if (tok == 16) RT(16, 1, 4, 4, 2, 2);
-    RT(16, 2, 4, 4, 2, 2);
+    if (tok == 32) RT(16, 2, 4, 4, 2, 2);
+    RT(16, 1, 4, 4, 2, 2);
   }
 #undef RT
 }

@@ -42,7 +42,8 @@ def check(s, logits, idx, gw, k, renorm):
 CASES = [(1, 128, 4, 2), (3, 256, 16, 1), (256, 128, 17, 8), (257, 384, 16, 3), (255, 2048, 64, 6), (1024, 128, 65, 4),
          (1025, 640, 64, 6), (1030, 128, 33, 2), (4096, 128, 129, 8), (4097, 256, 256, 8), (4100, 128, 32, 2),
          (5000, 128, 8, 2), (300, 256, 256, 8), (2000, 256, 200, 8), (7, 512, 100, 8), (4099, 128, 64, 6),
-         (4098, 256, 128, 4)]
+         (4098, 256, 128, 4), (8200, 128, 17, 2), (8195, 256, 40, 6), (8193, 128, 100, 4), (8199, 128, 256, 8),
+         (12400, 128, 32, 2), (12300, 128, 64, 6)]
 
 
 @pytest.mark.parametrize("T,d,E,k", CASES)
