@@ -574,10 +574,12 @@ static int dw_net(int E) { return E <= 16 ? 1 : E <= 32 ? 2 : E <= 64 ? 4 : E <=
 // Token chunks of the weight-gradient contraction, a multiple of 32 tokens each: as many as give the narrow kernel about
 // 256 workgroups for up to 16 experts and 1024 above (4 wavefronts x 16 x JJ columns each). The chunk is the length of an
 // fp32 accumulator and so sets the error of dW_router (T = 8192, d = 2048, E = 256: 3.0e-7 of its norm over 256 tokens,
-// 4.1e-7 over 512): the wide kernel takes the same chunks, though it would fill the chip with fewer. With 33 to 64 experts
-// it is left to chunks of 64 tokens and more: in shorter ones its long loop body runs once, from cold instruction caches
-// (partial sums and their sum, narrow and wide, 32-token chunks: E = 64, T = 300, d = 2048 16.3 and 18.7 us, T = 4,153,
-// d = 768 25.5 and 27.9; E = 128, T = 2,048, d = 2048 40.6 and 38.4, E = 256, T = 4,096, d = 512 47.4 and 38.7).
+// 4.1e-7 over 512): the wide kernel takes the same chunks, though it would fill the chip with fewer. Chunks of 32 tokens
+// are too short for its loop body, which then runs once, from cold instruction caches; more than 64 experts, whose
+// narrow kernel reads x several times, gain all the same once there are two of its wavefronts per SIMD (both launches,
+// us for narrow / wide: E = 256, bf16, T = 4096, d = 512 47 / 39, T = 1000, d = 1024 26.6 / 28.3; E = 128, T = 4096,
+// d = 1024 42.8 / 36.4, T = 2048, d = 512 24.1 / 25.5; E = 64, T = 2048, d = 2048 27.3 / 26.2, T = 3000, d = 1024
+// 24.7 / 25.0; E = 33, T = 3000, d = 2048 25.8 / 28.8).
 static void route_bwd_chunks(const moe_desc& d, int* nch, int* tpc, bool* wide) {
   const int E = d.n_experts;
   const int wg_cols = 64 * dw_cols_per_lane(dw_net(E));
@@ -588,7 +590,8 @@ static void route_bwd_chunks(const moe_desc& d, int* nch, int* tpc, bool* wide) 
   const int per = ((d.T + n - 1) / n + 31) / 32 * 32;
   *tpc = per;
   *nch = (d.T + per - 1) / per;
-  *wide = E > 64 || (E > 32 && per >= 64);
+  const int waves = dw_wide_cols(d) * ((E + 63) / 64) * *nch;  // of the wide kernel
+  *wide = E > 32 && (per >= 64 || (E > 64 && waves >= 2048));
 }
 
 size_t route_bwd_ws_bytes(const moe_desc& d) {

@@ -15,7 +15,7 @@ CASES = [  # T, d, E, k, shared, dtype
     (64, 128, 64, 1, 0, "f32"), (129, 640, 65, 4, 0, "bf16"), (1030, 256, 256, 8, 0, "bf16"), (16500, 256, 64, 2, 0, "bf16"),
     (8300, 256, 130, 4, 0, "f32"), (33000, 128, 33, 1, 0, "bf16"),
     (515, 128, 255, 6, 1, "f32"), (2050, 2048, 9, 2, 0, "bf16"), (2049, 2048, 11, 1, 1, "bf16"), (2050, 2048, 9, 3, 0, "bf16"),
-    (2047, 2048, 9, 2, 0, "bf16"),
+    (2047, 2048, 9, 2, 0, "bf16"), (1023, 2048, 250, 8, 0, "bf16"), (100, 1024, 100, 4, 0, "bf16"),
 ]
 
 
