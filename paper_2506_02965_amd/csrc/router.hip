@@ -616,7 +616,8 @@ static hipError_t route_bwd_t(const moe_desc& d, const void* x, const float* log
   int nch, tpc;
   bool wide;
   route_bwd_chunks(d, &nch, &tpc, &wide);
-  // one chunk (up to 32 tokens): its sums are the result, without the sum over chunks and its launch (6 us)
+  // one chunk (up to 32 tokens, or column blocks enough to fill the chip): its sums are the result, without the sum over
+  // chunks and its launch (6 us)
   float* part = nch == 1 ? dwr : (float*)ws;
   {
     KernelTimer kt("route_dw_partial", s);

@@ -7,7 +7,8 @@
 // CU. The weights are the MFMA's first operand, the activations' rows the second, so that a lane's four accumulators
 // are four consecutive output columns of one row.
 //   * stream_cols_kernel (up to 8 rows per group): a wavefront owns 16 or 32 output columns of 16 rows and shares nothing;
-//   * stream_rows_kernel (up to about 100): the wavefronts split the columns and share 32, 64 or 128 rows through LDS.
+//   * stream_rows_kernel (up to 32 to 200 rows, stream_pick): the wavefronts split the columns and share 32, 64 or 128
+//     rows through LDS.
 // Both sum over K in the order of the LDS tiles (one accumulator per output, 32 k per MFMA): the results are the same bits
 // whichever kernel a batch size selects.
 // The group, row chunk and columns of a workgroup come from the offsets alone (a scan over the wavefront), so no tile
